@@ -72,26 +72,29 @@ void reduce_code_kernel(ReduceCodeArgs a) {
     const int e = pair / kFusedCols;
     const int64_t col = col0 + pair % kFusedCols;
     if (col >= ca.q) continue;
-    const float* p = a.partials + static_cast<int64_t>(e) * a.blocks_per_part * ca.q + col;
+    const int64_t rows = a.m * a.n_eval;
+    const int64_t first = linear_row_block(rows, a.blocks, e * a.m);
+    const int count = static_cast<int>(linear_row_block(rows, a.blocks, (e + 1) * a.m - 1) - first) + 1;
+    const float* p = a.partials + (first + (a.aligned ? 0 : e)) * ca.q + col;
     // Loads go out 32 at a time (one memory latency per 32 partials); the
     // fp64 sum still runs in block order.
     double s = 0.0;
     int b = 0;
-    for (; b + 32 <= a.blocks_per_part; b += 32) {
+    for (; b + 32 <= count; b += 32) {
       float t[32];
 #pragma unroll
       for (int i = 0; i < 32; ++i) t[i] = p[static_cast<int64_t>(b + i) * ca.q];
 #pragma unroll
       for (int i = 0; i < 32; ++i) s += static_cast<double>(t[i]);
     }
-    for (; b + 8 <= a.blocks_per_part; b += 8) {
+    for (; b + 8 <= count; b += 8) {
       float t[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) t[i] = p[static_cast<int64_t>(b + i) * ca.q];
 #pragma unroll
       for (int i = 0; i < 8; ++i) s += static_cast<double>(t[i]);
     }
-    for (; b < a.blocks_per_part; ++b) s += static_cast<double>(p[static_cast<int64_t>(b) * ca.q]);
+    for (; b < count; ++b) s += static_cast<double>(p[static_cast<int64_t>(b) * ca.q]);
     const float g = static_cast<float>(s * a.inv_m);
     const int64_t k = static_cast<int64_t>(e) * a.part_stride + a.part_offset;
     for (int pl = 0; pl < a.plane_count; ++pl)

@@ -17,10 +17,14 @@
 namespace {
 
 constexpr size_t kAlign = 256;
-// Gradient grid: about pgc::linear_grad_target_blocks(d) blocks per launch,
-// never fewer than kMinRowsPerBlock rows per block.  The grid depends only on
-// the problem shape, so results do not depend on the device.
-constexpr int64_t kMinRowsPerBlock = 16;
+// The linear gradient's grid depends only on the problem shape, so results do not
+// depend on the device.  Iterations of a block from which its run may cross a
+// partition's end.
+constexpr int64_t kFlatIterations = 4;
+// pgc_step_noalloc takes the shapes whose partial sums would fit its fixed array
+// on a grid of about this many blocks of equal whole row counts within each
+// partition, at least so many rows per block.
+constexpr int64_t kNoallocBlocks = 1024, kNoallocMinRows = 16;
 // MLP head: about this many blocks per launch, rows per block a multiple of 64.
 constexpr int64_t kHeadTargetBlocks = 1024;
 // Ring slots and coded words are padded to a multiple of this many floats:
@@ -31,19 +35,52 @@ constexpr int64_t kSlotAlign = 256;
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
 
+// Grid of the MLP's head: blocks of rows_per_block rows within each partition.
 struct Grid {
   int32_t n_eval = 0;
   int32_t blocks_per_part = 0;
   int64_t rows_per_block = 0;
 };
 
-Grid make_grid(int64_t m, int32_t n_eval, int64_t target_blocks) {
-  Grid g;
+// Grid of the linear gradient: `blocks` equal runs of the n_eval * m evaluated rows.
+struct LinearGrid {
+  int32_t n_eval = 0;
+  int32_t blocks = 0;
+  bool aligned = false;   // no run crosses a partition's end
+  int64_t slots() const { return aligned ? blocks : blocks + int64_t{n_eval} - 1; }
+};
+
+// Partial sums by which pgc_step_noalloc takes or refuses a shape.
+int64_t noalloc_slots(int64_t m, int32_t n_eval) {
+  int64_t b = (kNoallocBlocks + n_eval - 1) / n_eval;
+  b = std::min(b, (m + kNoallocMinRows - 1) / kNoallocMinRows);
+  const int64_t rows = (m + b - 1) / b;
+  return n_eval * ((m + rows - 1) / rows);
+}
+
+// From kFlatIterations iterations per block on: the class's number of blocks, of
+// equal runs.  Fewer rows: equal blocks within each partition, as a run that
+// crosses into the next partition costs a block a second fold and a second
+// latency; and no block of less than an iteration, whose sums would only make
+// more to fold.
+LinearGrid make_linear_grid(int64_t m, int32_t n_eval, int64_t d) {
+  const pgc::LinearGradShape shape = pgc::linear_grad_shape(static_cast<int>(d));
+  LinearGrid g;
   g.n_eval = n_eval;
-  int64_t b = (target_blocks + n_eval - 1) / n_eval;
-  b = std::max<int64_t>(1, std::min<int64_t>(b, (m + kMinRowsPerBlock - 1) / kMinRowsPerBlock));
-  g.rows_per_block = (m + b - 1) / b;
-  g.blocks_per_part = static_cast<int32_t>((m + g.rows_per_block - 1) / g.rows_per_block);
+  int64_t blocks = shape.target_blocks;
+  bool flat = m * n_eval >= kFlatIterations * blocks * shape.rows_per_iteration;
+  // pgc_step_noalloc's array holds the sums of every shape it takes.
+  const int64_t fit = PGC_NOALLOC_SCRATCH_BYTES / (sizeof(float) * d);
+  if (flat && blocks + n_eval - 1 > fit && noalloc_slots(m, n_eval) <= fit) {
+    blocks = std::min(blocks, fit);
+    flat = false;
+  }
+  if (!flat) {
+    const int64_t iterations = (m + shape.rows_per_iteration - 1) / shape.rows_per_iteration;
+    blocks = n_eval * std::max<int64_t>(1, std::min(blocks / n_eval, iterations));
+  }
+  g.blocks = static_cast<int32_t>(blocks);
+  g.aligned = blocks % n_eval == 0;
   return g;
 }
 
@@ -76,12 +113,12 @@ struct pgc_ctx {
   // Workspace layout (byte offsets).
   int planes = 0, n_coded = 0;
   int64_t ld = 0;             // floats between ring slots / coded words
-  Grid warm, pipe;            // linear gradient grids
+  LinearGrid warm, pipe;      // linear gradient grids
   Grid head_warm, head_pipe;  // MLP head grids
   int64_t kpad = 0, m_pad = 0, pstride = 0;
   size_t off_ring = 0, off_coded = 0, off_decoded = 0, off_partials = 0, off_coef = 0, ws_need = 0;
   size_t off_w1t = 0, off_w2t = 0, off_w2p = 0, off_h = 0, off_dz1 = 0;
-  size_t partials_bytes = 0;  // linear models: block partial sums of the larger gradient grid
+  size_t noalloc_bytes = 0;   // linear models: the partial sums pgc_step_noalloc accounts for
   char* ws = nullptr;
   size_t ws_bytes = 0;
   hipStream_t stream = nullptr;
@@ -147,14 +184,12 @@ void compute_layout(pgc_ctx* ctx) {
     ctx->off_dz1 = take(2 * static_cast<size_t>(n) * hidden * ctx->m_pad);
     ctx->off_partials = take(sizeof(float) * static_cast<size_t>(head_blocks * ctx->pstride));
   } else {
-    const int64_t target = pgc::linear_grad_target_blocks(static_cast<int>(q));
-    ctx->warm = make_grid(ctx->m, n, target);
-    ctx->pipe = make_grid(ctx->m, n_pipe, target);
-    const int64_t max_blocks =
-        std::max<int64_t>(static_cast<int64_t>(ctx->warm.n_eval) * ctx->warm.blocks_per_part,
-                          static_cast<int64_t>(ctx->pipe.n_eval) * ctx->pipe.blocks_per_part);
-    ctx->partials_bytes = sizeof(float) * static_cast<size_t>(max_blocks) * q;
-    ctx->off_partials = take(ctx->partials_bytes);
+    ctx->warm = make_linear_grid(ctx->m, n, q);
+    ctx->pipe = make_linear_grid(ctx->m, n_pipe, q);
+    ctx->off_partials =
+        take(sizeof(float) * static_cast<size_t>(std::max(ctx->warm.slots(), ctx->pipe.slots()) * q));
+    ctx->noalloc_bytes =
+        sizeof(float) * static_cast<size_t>(std::max(noalloc_slots(ctx->m, n), noalloc_slots(ctx->m, n_pipe)) * q);
   }
   ctx->ws_need = off;
 }
@@ -527,37 +562,38 @@ pgc::CodeArgs code_args(pgc_ctx* ctx, const pgc::Decode& dec, float* w, float lr
 int linear_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc::Decode& dec, float lr,
                 bool warm, int32_t part_stride, int32_t part_offset, int plane_first, int plane_count,
                 float* partials) {
-  const Grid& grid = warm ? ctx->warm : ctx->pipe;
+  const LinearGrid& grid = warm ? ctx->warm : ctx->pipe;
   pgc::LinearGradArgs ga{};
   ga.X = static_cast<const float*>(X);
   ga.y = static_cast<const float*>(y);
   ga.w = w;
   ga.partials = partials;
   ga.m = ctx->m;
-  ga.rows_per_block = grid.rows_per_block;
+  ga.rows = ctx->m * grid.n_eval;
   ga.d = static_cast<int32_t>(ctx->d);
-  ga.blocks_per_part = grid.blocks_per_part;
-  ga.n_eval = grid.n_eval;
+  ga.blocks = grid.blocks;
+  ga.aligned = grid.aligned ? 1 : 0;
+  ga.spread = pgc::linear_spread_starts(ga.rows, ga.blocks, ctx->d) ? 1 : 0;
   ga.part_stride = part_stride;
   ga.part_offset = part_offset;
   ga.model = ctx->cfg.model;
-  const bool aligned16 = reinterpret_cast<uintptr_t>(X) % 16 == 0 &&
-                         reinterpret_cast<uintptr_t>(w) % 16 == 0;
 
   pgc::ReduceCodeArgs ra{};
   ra.code = code_args(ctx, dec, w, lr);
   ra.ring = ws_ptr<float>(ctx, ctx->off_ring);
   ra.partials = ga.partials;
   ra.inv_m = 1.0 / static_cast<double>(ctx->m);
+  ra.m = ctx->m;
   ra.n_eval = grid.n_eval;
-  ra.blocks_per_part = grid.blocks_per_part;
+  ra.blocks = grid.blocks;
+  ra.aligned = ga.aligned;
   ra.part_stride = part_stride;
   ra.part_offset = part_offset;
   ra.plane_first = plane_first;
   ra.plane_count = plane_count;
 
   int st = timed_launch(ctx, PGC_KERNEL_GRADIENT, "gradient kernel",
-                        [&] { return pgc::launch_linear_gradient(ga, aligned16, ctx->stream); });
+                        [&] { return pgc::launch_linear_gradient(ga, ctx->stream); });
   if (st != PGC_OK) return st;
   return timed_launch(ctx, PGC_KERNEL_CODE, "reduce/code kernel",
                       [&] { return pgc::launch_reduce_code(ra, ctx->stream); });
@@ -673,7 +709,7 @@ int mlp_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc::De
 
 namespace pgc {
 
-size_t linear_partials_bytes(const pgc_ctx* ctx) { return ctx->partials_bytes; }
+size_t noalloc_partials_bytes(const pgc_ctx* ctx) { return ctx->noalloc_bytes; }
 
 bool context_is_linear(const pgc_ctx* ctx) { return ctx->configured && is_linear(ctx->cfg.model); }
 
@@ -711,14 +747,14 @@ int step_impl(pgc_ctx* ctx, const void* X, const void* y, float* w, const uint8_
   const int plane_first = fr ? 0 : o;
   const int plane_count = (!fr && warm) ? c : 1;
 
-  bool aligned16 = false;
   if (ctx->cfg.model == PGC_MLP) {
     if (reinterpret_cast<uintptr_t>(X) % 16 != 0 || reinterpret_cast<uintptr_t>(y) % 4 != 0 ||
         reinterpret_cast<uintptr_t>(w) % 4 != 0)
       return fail(ctx, PGC_EINVAL, "MLP: X must be 16-byte aligned, y and w 4-byte aligned");
   } else {
-    aligned16 = reinterpret_cast<uintptr_t>(X) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0;
-    if (!pgc::linear_grad_shape(static_cast<int>(ctx->d), aligned16).supported)
+    const bool aligned16 =
+        reinterpret_cast<uintptr_t>(X) % 16 == 0 && reinterpret_cast<uintptr_t>(w) % 16 == 0;
+    if (!pgc::linear_grad_supported(static_cast<int>(ctx->d), aligned16))
       return fail(ctx, PGC_EINVAL, "d = " + std::to_string(ctx->d) +
                                        " needs d % 4 == 0 and 16-byte aligned X and w");
   }

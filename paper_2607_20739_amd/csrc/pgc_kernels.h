@@ -9,38 +9,55 @@
 
 namespace pgc {
 
+// First of block b's rows when `blocks` blocks share `rows` rows (b = blocks: the end).
+__host__ __device__ inline int64_t linear_block_row(int64_t rows, int64_t blocks, int64_t b) {
+  return b * rows / blocks;
+}
+// The block whose rows hold row r.
+__host__ __device__ inline int64_t linear_row_block(int64_t rows, int64_t blocks, int64_t r) {
+  return ((r + 1) * blocks - 1) / rows;
+}
+
 // Per-partition gradient of a linear model (Sec. III with a mean over each
-// partition's rows): for each evaluated partition k = e * part_stride +
-// part_offset, e < n_eval, block b of that partition sums
+// partition's rows).  The rows of the evaluated partitions k = e * part_stride +
+// part_offset, e < n_eval, are counted through, and each of `blocks` blocks takes
+// an equal run of them.  For every partition that block b's run touches it sums
 //   slope(x_r . w, y_r) * x_r
-// over its rows r and writes the fp32 sum to partials[(e * blocks_per_part + b) * d].
+// over its rows there and writes the fp32 sum to partials[slot * d].  When the runs
+// never cross a partition's end (aligned: n_eval divides blocks) slot = b, else
+// slot = b + e, which grows by one or two from each sum to the next.
 struct LinearGradArgs {
   const float* X;          // N x d row-major
   const float* y;          // N
   const float* w;          // d
-  float* partials;         // n_eval * blocks_per_part * d
+  float* partials;         // (blocks + (aligned ? 0 : n_eval - 1)) * d
   int64_t m;               // rows per partition
-  int64_t rows_per_block;  // contiguous rows handled by one block
+  int64_t rows;            // n_eval * m
   int32_t d;
-  int32_t blocks_per_part;
-  int32_t n_eval;
+  int32_t blocks;          // at most rows
+  int32_t aligned;
+  int32_t spread;          // start each block at a scattered place in its run
   int32_t part_stride;
   int32_t part_offset;
   int32_t model;           // PGC_LOGISTIC or PGC_LSQ
 };
 
-// Launch shape the gradient kernel uses for d (the caller sizes partials with it).
+// Whether the step takes d features: up to PGC_MAX_LINEAR_D when d % 4 == 0 and X
+// and w are 16-byte aligned, else up to PGC_MAX_LINEAR_D_UNALIGNED.
+bool linear_grad_supported(int d, bool aligned16);
+// Blocks per launch that the gradient grid aims for, and the rows a block takes at
+// once (by d only, so the grid, and with it every result, is independent of pointer
+// alignment and device).
 struct LinearGradShape {
-  int threads;       // threads per block
-  int vec_width;     // 4 (float4 loads) or 1
-  bool supported;
+  int target_blocks;
+  int rows_per_iteration;
 };
-LinearGradShape linear_grad_shape(int d, bool aligned16);
-// Blocks per launch the gradient grid aims for (depends on d only, so the grid,
-// and with it every result, is independent of pointer alignment and device).
-int linear_grad_target_blocks(int d);
+LinearGradShape linear_grad_shape(int d);
 
-hipError_t launch_linear_gradient(const LinearGradArgs& a, bool aligned16, hipStream_t s);
+// Whether the blocks' runs are better read from scattered starts.
+bool linear_spread_starts(int64_t rows, int64_t blocks, int64_t d);
+
+hipError_t launch_linear_gradient(const LinearGradArgs& a, hipStream_t s);
 
 // Encode, masked decode and update, column by column:
 //   coded_j = sum_o coef(j, o) * ring[slot(j, o)]          (Sec. IV-A, V-A, V-B)
@@ -69,15 +86,18 @@ hipError_t launch_code(const CodeArgs& a, hipStream_t s);
 // The linear models' block partials folded into the ring, then the code step,
 // in one launch: for each evaluated e (partition k = e * part_stride +
 // part_offset) and p < plane_count,
-//   ring[(plane_first + p) * n + k][:] = inv_m * sum_b partials[e][b][:]
-// (fp64, block order), then encode / decode / update of the same columns.
+//   ring[(plane_first + p) * n + k][:] = inv_m * sum of e's partials
+// (fp64, block order; the gradient kernel's slots), then encode / decode / update
+// of the same columns.
 struct ReduceCodeArgs {
   CodeArgs code;
   float* ring;             // the ring code.ring reads, written here first
-  const float* partials;   // n_eval x blocks_per_part x q
+  const float* partials;   // as LinearGradArgs::partials
   double inv_m;
+  int64_t m;
   int32_t n_eval;
-  int32_t blocks_per_part;
+  int32_t blocks;
+  int32_t aligned;
   int32_t part_stride;
   int32_t part_offset;
   int32_t plane_first;

@@ -1,6 +1,6 @@
-// Reductions over the 16-lane rows of a gfx950 wave64, built from DPP lane
-// moves, which go register to register (no LDS permute round trip).  Every
-// reduction has a fixed order, so results are bitwise reproducible.
+// Reductions over aligned groups of lanes of a gfx950 wave64, within 16-lane rows
+// built from DPP lane moves, which go register to register (no LDS permute round
+// trip).  Every reduction has a fixed order, so results are bitwise reproducible.
 #pragma once
 #include <hip/hip_runtime.h>
 
@@ -30,6 +30,19 @@ __device__ __forceinline__ float row16_sum(float v) {
   v += dpp_move<kDppSwap2>(v);
   v += dpp_move<kDppHalfMirror>(v);
   return v + dpp_move<kDppMirror>(v);
+}
+
+// Sum over each aligned group of LANES lanes (a power of two up to 64); every
+// lane of a group ends with the same total.
+template <int LANES>
+__device__ __forceinline__ float lane_group_sum(float v) {
+  if constexpr (LANES >= 2) v += dpp_move<kDppSwap1>(v);
+  if constexpr (LANES >= 4) v += dpp_move<kDppSwap2>(v);
+  if constexpr (LANES >= 8) v += dpp_move<kDppHalfMirror>(v);
+  if constexpr (LANES >= 16) v += dpp_move<kDppMirror>(v);
+  if constexpr (LANES >= 32) v += __shfl_xor(v, 16, 64);
+  if constexpr (LANES >= 64) v += __shfl_xor(v, 32, 64);
+  return v;
 }
 
 }  // namespace pgc

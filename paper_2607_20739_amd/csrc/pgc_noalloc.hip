@@ -47,7 +47,7 @@ extern "C" int pgc_step_noalloc(pgc_ctx* ctx, const void* X, const void* y, floa
   if (!pgc::context_is_configured(ctx)) return pgc::set_error(ctx, PGC_ESTATE, "pgc_configure first");
   if (!pgc::context_is_linear(ctx))
     return pgc::set_error(ctx, PGC_EINVAL, "pgc_step_noalloc runs the linear models only (PGC_LOGISTIC, PGC_LSQ)");
-  const size_t need = pgc::linear_partials_bytes(ctx);
+  const size_t need = pgc::noalloc_partials_bytes(ctx);
   if (need > PGC_NOALLOC_SCRATCH_BYTES) {
     const std::string msg = "pgc_step_noalloc: the gradient's block partials need " + std::to_string(need) +
                             " bytes, more than the fixed scratch of " +

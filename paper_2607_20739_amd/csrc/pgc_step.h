@@ -10,14 +10,14 @@
 namespace pgc {
 
 // pgc_step with the linear models' block partials at `partials` (device; at
-// least linear_partials_bytes(ctx) bytes), or in the bound workspace when
+// least noalloc_partials_bytes(ctx) bytes), or in the bound workspace when
 // `partials` is null.  Same checks, errors and effects as pgc_step.
 int step_impl(pgc_ctx* ctx, const void* X, const void* y, float* w, const uint8_t* straggler_mask,
               float lr, float* partials);
 
-// Bytes of block partial sums a linear-model step of the configured context
-// writes at most (the larger of the warm-up and pipelined gradient grids).
-size_t linear_partials_bytes(const pgc_ctx* ctx);
+// Bytes of block partial sums by which pgc_step_noalloc accepts or refuses the
+// configured context: at least what a linear-model step of it writes.
+size_t noalloc_partials_bytes(const pgc_ctx* ctx);
 
 bool context_is_configured(const pgc_ctx* ctx);
 bool context_has_workspace(const pgc_ctx* ctx);

@@ -1,0 +1,134 @@
+"""The linear gradient kernel at the edges of its launch shapes.
+
+Its shape follows the row length (lanes, waves and 16-byte chunks of a row), and
+its blocks take equal runs of the evaluated rows whatever the partitions, so the
+cases are row lengths on both sides of every class, with row counts that leave
+remainders everywhere, and few, many, long and very short partitions.  One step
+from w = 0 at lr = 1 gives w = -ghat, compared with the same mean gradient in
+float64 within the fp32 bar (1e-5 normwise).
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2607_20739_amd as P
+
+from _parity import FP32_TOL, normwise_error
+
+pytestmark = pytest.mark.gpu
+
+# Largest 16-byte chunk count of each class of row lengths.
+CLASSES = [1, 2, 4, 6, 8, 12, 16, 32, 48, 56, 64, 96, 112, 128, 192, 224, 256, 320, 384, 512, 640, 768, 896,
+           1024, 1280, 1536, 2048, 2560, 3072, 4096, 5120, 6144, 7168, 8192]
+LENGTHS = sorted({d for c in CLASSES for d in (4 * c - 3, 4 * c - 1, 4 * c, 4 * c + 1, 4 * c + 4)
+                  if d <= 8192 or (d % 4 == 0 and d <= 32768)} | {2, 3})
+
+
+def _announce(what):
+    print("\n[gpu case] " + what, flush=True)
+
+
+def _mean_gradient(model, X, y, w0):
+    X, y, w0 = X.double(), y.double(), w0.double()
+    z = X @ w0
+    slope = (torch.sigmoid(z) if model == "logistic" else z) - y
+    return (X.t() @ slope / X.shape[0]).cpu().numpy()
+
+
+def _one_step(scheme, model, n, c, X, y, w0, pipelined=True, steps=1):
+    sess = P.PGCSession(scheme, n, c, model, X.shape[0], X.shape[1], pipelined=pipelined)
+    try:
+        w = w0.clone()
+        for _ in range(steps):
+            sess.step(X, y, w, np.zeros(n, np.uint8), 1.0)
+            ghat = sess.decoded()
+        torch.cuda.synchronize()
+        return ghat, w
+    finally:
+        sess.close()
+
+
+@pytest.mark.parametrize("chunk", range(0, len(LENGTHS), 17))
+def test_row_lengths_around_every_class(chunk):
+    for i, d in enumerate(LENGTHS[chunk:chunk + 17]):
+        n, m = ((7, 150), (3, 333), (16, 75))[i % 3]
+        model = ("logistic", "lsq")[i % 2]
+        _announce("d=%d n=%d m=%d %s" % (d, n, m, model))
+        g = torch.Generator(device="cuda")
+        g.manual_seed(d)
+        X = torch.randn(n * m, d, generator=g, device="cuda")
+        y = torch.randint(2, (n * m,), generator=g, device="cuda").float()
+        w0 = 0.5 * torch.randn(d, generator=g, device="cuda") / d ** 0.5
+        ghat, w = _one_step("FR", model, n, 1, X, y, w0)
+        ref = _mean_gradient(model, X, y, w0)
+        assert normwise_error(ghat.cpu().numpy(), ref) <= FP32_TOL, d
+        assert normwise_error(w.cpu().numpy(), w0.double().cpu().numpy() - ref) <= FP32_TOL, d
+
+
+@pytest.mark.parametrize("n,m", [(1, 1), (1, 4099), (2, 15), (5, 17), (12, 8191), (31, 3), (64, 16), (100, 129),
+                                 (200, 21), (255, 33), (256, 1), (256, 257)])
+@pytest.mark.parametrize("d", [20, 1001, 2052, 10240])
+def test_blocks_that_cross_partitions(n, m, d):
+    """Every ring slot holds its own partition's gradient, whatever blocks its rows fell to."""
+    _announce("n=%d m=%d d=%d" % (n, m, d))
+    m = min(m, max(1, (1 << 27) // (n * d)))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n * m)
+    X = torch.randn(n * m, d, generator=g, device="cuda")
+    y = torch.randn(n * m, generator=g, device="cuda")
+    w = torch.zeros(d, device="cuda")
+    sess = P.PGCSession("IS_SGD", n, 1, "lsq", n * m, d)
+    try:
+        sess.step(X, y, w, np.zeros(n, np.uint8), 0.0)
+        for k in sorted({0, 1 % n, n // 2, n - 1}):
+            rows = slice(k * m, (k + 1) * m)
+            ref = _mean_gradient("lsq", X[rows], y[rows], w)
+            assert normwise_error(sess.ring(k, 0).cpu().numpy(), ref) <= FP32_TOL, k
+    finally:
+        sess.close()
+
+
+def test_any_base_address_gives_the_same_bits():
+    n, m, d = 6, 211, 1000
+    _announce("X and w at every float offset, d=%d" % d)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    X = torch.randn(n * m, d, generator=g, device="cuda")
+    y = torch.randint(2, (n * m,), generator=g, device="cuda").float()
+    w0 = torch.randn(d, generator=g, device="cuda") / d ** 0.5
+    ref = None
+    for off in range(4):
+        Xo = torch.empty(n * m * d + 4, device="cuda")[off:off + n * m * d].view(n * m, d).copy_(X)
+        wo = torch.empty(d + 4, device="cuda")[off:off + d].copy_(w0)
+        sess = P.PGCSession("FR", n, 3, "logistic", n * m, d)
+        try:
+            for _ in range(3):
+                sess.step(Xo, y, wo, np.zeros(n, np.uint8), 0.1)
+            got = wo.clone()
+        finally:
+            sess.close()
+        ref = got if ref is None else ref
+        assert torch.equal(got, ref), off
+
+
+@pytest.mark.parametrize("d", [7, 69, 1001, 4099])
+def test_infinite_features_reach_only_what_they_touch(d):
+    """An infinite feature makes its row's z infinite (the sigmoid's limit), and its own column
+    infinite; the floats the last chunk shares with another lane add nothing of their own."""
+    n, m = 2, 40
+    _announce("infinite feature, d=%d" % d)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    X = torch.randn(n * m, d, generator=g, device="cuda")
+    y = torch.zeros(n * m, device="cuda")
+    w0 = torch.ones(d, device="cuda") / d
+    for col in (0, d - 5, d - 4, d - 3, d - 1):
+        Xi = X.clone()
+        Xi[3, col] = float("inf")
+        ghat, _ = _one_step("FR", "logistic", n, 1, Xi, y, w0)
+        ref = _mean_gradient("logistic", Xi, y, w0)
+        got = ghat.cpu().numpy()
+        fine = np.isfinite(ref)
+        assert np.array_equal(np.isfinite(got), fine) and fine.sum() == d - 1, col
+        assert normwise_error(got[fine], ref[fine]) <= FP32_TOL, col
