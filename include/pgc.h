@@ -77,8 +77,8 @@ enum pgc_kernel {
   PGC_KERNEL_CODE = 2,        /* encode + masked decode + update (linear models: also folds the
                                  gradient kernel's partial sums into the ring first) */
   PGC_KERNEL_MLP_CAST = 3,    /* MLP: bf16 copies of W1 and W2 */
-  PGC_KERNEL_MLP_FORWARD = 4, /* MLP: H = relu(X W1 + b1), bf16 MFMA GEMM */
-  PGC_KERNEL_MLP_HEAD = 5,    /* MLP: logits, softmax, dZ2, dZ1 and the small-layer gradients */
+  PGC_KERNEL_MLP_FORWARD = 4, /* MLP: forward, softmax, dZ1 and the small-layer gradients, one bf16 MFMA kernel */
+  PGC_KERNEL_MLP_HEAD = 5,    /* MLP: part of PGC_KERNEL_MLP_FORWARD (no launch of its own) */
   PGC_KERNEL_MLP_WGRAD = 6,   /* MLP: dW1 = X^T dZ1 per partition, bf16 MFMA GEMM */
   PGC_KERNEL_COUNT = 7
 };

@@ -25,8 +25,6 @@ constexpr int64_t kFlatIterations = 4;
 // on a grid of about this many blocks of equal whole row counts within each
 // partition, at least so many rows per block.
 constexpr int64_t kNoallocBlocks = 1024, kNoallocMinRows = 16;
-// MLP head: about this many blocks per launch, rows per block a multiple of 64.
-constexpr int64_t kHeadTargetBlocks = 1024;
 // Ring slots and coded words are padded to a multiple of this many floats:
 // every slot starts 1 KiB aligned, and the code kernel's 256-column blocks
 // cover a slot exactly (never spilling into the next one).
@@ -34,13 +32,6 @@ constexpr int64_t kSlotAlign = 256;
 
 size_t align_up(size_t x) { return (x + kAlign - 1) / kAlign * kAlign; }
 int64_t round_up(int64_t x, int64_t a) { return (x + a - 1) / a * a; }
-
-// Grid of the MLP's head: blocks of rows_per_block rows within each partition.
-struct Grid {
-  int32_t n_eval = 0;
-  int32_t blocks_per_part = 0;
-  int64_t rows_per_block = 0;
-};
 
 // Grid of the linear gradient: `blocks` equal runs of the n_eval * m evaluated rows.
 struct LinearGrid {
@@ -84,17 +75,6 @@ LinearGrid make_linear_grid(int64_t m, int32_t n_eval, int64_t d) {
   return g;
 }
 
-// Head grid of the MLP: blocks of a multiple of 64 rows over the m_pad rows.
-Grid make_head_grid(int64_t m_pad, int32_t n_eval) {
-  Grid g;
-  g.n_eval = n_eval;
-  int64_t b = (kHeadTargetBlocks + n_eval - 1) / n_eval;
-  b = std::max<int64_t>(1, std::min<int64_t>(b, m_pad / 64));
-  g.rows_per_block = round_up((m_pad + b - 1) / b, 64);
-  g.blocks_per_part = static_cast<int32_t>((m_pad + g.rows_per_block - 1) / g.rows_per_block);
-  return g;
-}
-
 struct Timed {
   hipEvent_t start = nullptr, stop = nullptr;
   int kernel = 0;
@@ -114,10 +94,10 @@ struct pgc_ctx {
   int planes = 0, n_coded = 0;
   int64_t ld = 0;             // floats between ring slots / coded words
   LinearGrid warm, pipe;      // linear gradient grids
-  Grid head_warm, head_pipe;  // MLP head grids
-  int64_t kpad = 0, m_pad = 0, pstride = 0;
+  pgc::MlpRowsGrid rows_warm, rows_pipe;   // MLP rows kernel grids
+  int64_t kslices = 0, m_pad = 0, pstride = 0;
   size_t off_ring = 0, off_coded = 0, off_decoded = 0, off_partials = 0, off_coef = 0, ws_need = 0;
-  size_t off_w1t = 0, off_w2t = 0, off_w2p = 0, off_h = 0, off_dz1 = 0;
+  size_t off_w1f = 0, off_w2t = 0, off_w2p = 0, off_dz1 = 0;
   size_t noalloc_bytes = 0;   // linear models: the partial sums pgc_step_noalloc accounts for
   char* ws = nullptr;
   size_t ws_bytes = 0;
@@ -169,20 +149,18 @@ void compute_layout(pgc_ctx* ctx) {
   ctx->off_coef = take(sizeof(double) * ctx->coef.size());
   if (ctx->cfg.model == PGC_MLP) {
     const int64_t hidden = ctx->cfg.hidden;
-    ctx->kpad = round_up(ctx->cfg.d_in, 64);   // the forward GEMM's K step
+    ctx->kslices = (ctx->cfg.d_in + 31) / 32;   // the forward GEMM's K step
     ctx->m_pad = round_up(ctx->m, 64);   // the weight-gradient GEMM's K step
     ctx->pstride = (pgc::kMlpMaxClasses + 1) * hidden + pgc::kMlpMaxClasses;
-    ctx->head_warm = make_head_grid(ctx->m_pad, n);
-    ctx->head_pipe = make_head_grid(ctx->m_pad, n_pipe);
-    const int64_t head_blocks =
-        std::max<int64_t>(static_cast<int64_t>(ctx->head_warm.n_eval) * ctx->head_warm.blocks_per_part,
-                          static_cast<int64_t>(ctx->head_pipe.n_eval) * ctx->head_pipe.blocks_per_part);
-    ctx->off_w1t = take(2 * static_cast<size_t>(hidden * ctx->kpad));
+    const int32_t ks = static_cast<int32_t>(ctx->kslices);
+    ctx->rows_warm = pgc::mlp_rows_grid(ctx->m_pad, n, ks, static_cast<int32_t>(hidden));
+    ctx->rows_pipe = pgc::mlp_rows_grid(ctx->m_pad, n_pipe, ks, static_cast<int32_t>(hidden));
+    const int64_t slots = std::max(ctx->rows_warm.blocks + int64_t{n} - 1, ctx->rows_pipe.blocks + int64_t{n_pipe} - 1);
+    ctx->off_w1f = take(2 * static_cast<size_t>(hidden * ctx->kslices * 32));
     ctx->off_w2t = take(2 * static_cast<size_t>(pgc::kMlpMaxClasses * hidden));
     ctx->off_w2p = take(2 * static_cast<size_t>(hidden * pgc::kMlpMaxClasses));
-    ctx->off_h = take(2 * static_cast<size_t>(n) * ctx->m_pad * hidden);
     ctx->off_dz1 = take(2 * static_cast<size_t>(n) * hidden * ctx->m_pad);
-    ctx->off_partials = take(sizeof(float) * static_cast<size_t>(head_blocks * ctx->pstride));
+    ctx->off_partials = take(sizeof(float) * static_cast<size_t>(slots * ctx->pstride));
   } else {
     ctx->warm = make_linear_grid(ctx->m, n, q);
     ctx->pipe = make_linear_grid(ctx->m, n_pipe, q);
@@ -599,56 +577,44 @@ int linear_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc:
                       [&] { return pgc::launch_reduce_code(ra, ctx->stream); });
 }
 
-// a4-a5 for the MLP: cast, forward, head, weight gradient, small-part reduce,
-// then copies of the slot into the other planes at the CR warm-up.
+// a4-a5 for the MLP: cast, rows (forward to dZ1), weight gradient, small-part
+// reduce, then copies of the slot into the other planes at the CR warm-up.
 int mlp_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc::Decode& dec, float lr,
-             bool warm, int32_t part_stride, int32_t part_offset, int plane_first, int plane_count) {
-  const Grid& hg = warm ? ctx->head_warm : ctx->head_pipe;
+             bool warm, int32_t n_eval, int32_t part_stride, int32_t part_offset, int plane_first, int plane_count) {
+  const pgc::MlpRowsGrid& grid = warm ? ctx->rows_warm : ctx->rows_pipe;
   const int32_t d_in = ctx->cfg.d_in, hidden = ctx->cfg.hidden, classes = ctx->cfg.classes;
   const int64_t w1 = static_cast<int64_t>(d_in) * hidden;
-  __bf16* W1T = ws_ptr<__bf16>(ctx, ctx->off_w1t);
+  __bf16* W1F = ws_ptr<__bf16>(ctx, ctx->off_w1f);
   __bf16* W2T = ws_ptr<__bf16>(ctx, ctx->off_w2t);
   __bf16* W2p = ws_ptr<__bf16>(ctx, ctx->off_w2p);
-  __bf16* H = ws_ptr<__bf16>(ctx, ctx->off_h);
   __bf16* dZ1 = ws_ptr<__bf16>(ctx, ctx->off_dz1);
   float* ring = ws_ptr<float>(ctx, ctx->off_ring);
   float* partials = ws_ptr<float>(ctx, ctx->off_partials);
 
-  pgc::MlpCastArgs cast{w, W1T, W2T, W2p, d_in, static_cast<int32_t>(ctx->kpad), hidden, classes};
-  pgc::MlpForwardArgs fw{};
-  fw.X = static_cast<const __bf16*>(X);
-  fw.W1T = W1T;
-  fw.b1 = w + w1;
-  fw.H = H;
-  fw.m = ctx->m;
-  fw.m_pad = ctx->m_pad;
-  fw.d_in = d_in;
-  fw.kpad = static_cast<int32_t>(ctx->kpad);
-  fw.hidden = hidden;
-  fw.n_eval = hg.n_eval;
-  fw.part_stride = part_stride;
-  fw.part_offset = part_offset;
-  pgc::MlpHeadArgs hd{};
-  hd.H = H;
-  hd.y = static_cast<const int32_t*>(y);
-  hd.W2T = W2T;
-  hd.W2p = W2p;
-  hd.b2 = w + w1 + hidden + static_cast<int64_t>(hidden) * classes;
-  hd.dZ1 = dZ1;
-  hd.partials = partials;
-  hd.m = ctx->m;
-  hd.m_pad = ctx->m_pad;
-  hd.rows_per_block = hg.rows_per_block;
-  hd.inv_m = static_cast<float>(1.0 / static_cast<double>(ctx->m));
-  hd.hidden = hidden;
-  hd.classes = classes;
-  hd.blocks_per_part = hg.blocks_per_part;
-  hd.n_eval = hg.n_eval;
-  hd.part_stride = part_stride;
-  hd.part_offset = part_offset;
-  hd.pstride = static_cast<int32_t>(ctx->pstride);
+  pgc::MlpCastArgs cast{w, W1F, W2T, W2p, d_in, static_cast<int32_t>(ctx->kslices), hidden, classes};
+  pgc::MlpRowsArgs ra{};
+  ra.X = static_cast<const __bf16*>(X);
+  ra.y = static_cast<const int32_t*>(y);
+  ra.W1F = W1F;
+  ra.W2T = W2T;
+  ra.W2p = W2p;
+  ra.b1 = w + w1;
+  ra.b2 = w + w1 + hidden + static_cast<int64_t>(hidden) * classes;
+  ra.dZ1 = dZ1;
+  ra.partials = partials;
+  ra.m = ctx->m;
+  ra.m_pad = ctx->m_pad;
+  ra.pstride = ctx->pstride;
+  ra.inv_m = static_cast<float>(1.0 / static_cast<double>(ctx->m));
+  ra.d_in = d_in;
+  ra.kslices = static_cast<int32_t>(ctx->kslices);
+  ra.classes = classes;
+  ra.n_eval = n_eval;
+  ra.blocks = grid.blocks;
+  ra.part_stride = part_stride;
+  ra.part_offset = part_offset;
   pgc::MlpWgradArgs wg{};
-  wg.X = fw.X;
+  wg.X = ra.X;
   wg.dZ1 = dZ1;
   wg.ring = ring;
   wg.m = ctx->m;
@@ -658,7 +624,7 @@ int mlp_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc::De
   wg.hidden = hidden;
   wg.n = ctx->n;
   wg.plane = plane_first;
-  wg.n_eval = hg.n_eval;
+  wg.n_eval = n_eval;
   wg.part_stride = part_stride;
   wg.part_offset = part_offset;
   pgc::MlpReduceArgs rd{};
@@ -670,20 +636,18 @@ int mlp_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc::De
   rd.classes = classes;
   rd.n = ctx->n;
   rd.plane = plane_first;
-  rd.n_eval = hg.n_eval;
-  rd.blocks_per_part = hg.blocks_per_part;
+  rd.n_eval = n_eval;
+  rd.tiles_per_part = grid.tiles_per_part;
+  rd.blocks = grid.blocks;
   rd.part_stride = part_stride;
   rd.part_offset = part_offset;
-  rd.pstride = static_cast<int32_t>(ctx->pstride);
+  rd.pstride = ctx->pstride;
 
-  int st = timed_launch(ctx, PGC_KERNEL_MLP_CAST, "MLP cast kernels",
+  int st = timed_launch(ctx, PGC_KERNEL_MLP_CAST, "MLP cast kernel",
                         [&] { return pgc::launch_mlp_cast(cast, ctx->stream); });
   if (st == PGC_OK)
-    st = timed_launch(ctx, PGC_KERNEL_MLP_FORWARD, "MLP forward kernel",
-                      [&] { return pgc::launch_mlp_forward(fw, ctx->stream); });
-  if (st == PGC_OK)
-    st = timed_launch(ctx, PGC_KERNEL_MLP_HEAD, "MLP head kernel",
-                      [&] { return pgc::launch_mlp_head(hd, ctx->stream); });
+    st = timed_launch(ctx, PGC_KERNEL_MLP_FORWARD, "MLP rows kernel",
+                      [&] { return pgc::launch_mlp_rows(ra, hidden, grid.shape, ctx->stream); });
   if (st == PGC_OK)
     st = timed_launch(ctx, PGC_KERNEL_MLP_WGRAD, "MLP weight-gradient kernel",
                       [&] { return pgc::launch_mlp_wgrad(wg, ctx->stream); });
@@ -761,7 +725,7 @@ int step_impl(pgc_ctx* ctx, const void* X, const void* y, float* w, const uint8_
   // A host-side range per step, for profilers that record roctx markers.
   roctxRangePushA(warm ? "pgc_step (warm-up)" : "pgc_step");
   const int st = ctx->cfg.model == PGC_MLP
-                     ? mlp_step(ctx, X, y, w, dec, lr, warm, part_stride, part_offset, plane_first, plane_count)
+                     ? mlp_step(ctx, X, y, w, dec, lr, warm, (fr && !warm) ? ctx->n / c : ctx->n, part_stride, part_offset, plane_first, plane_count)
                      : linear_step(ctx, X, y, w, dec, lr, warm, part_stride, part_offset, plane_first, plane_count,
                                    partials ? partials : ws_ptr<float>(ctx, ctx->off_partials));
   roctxRangePop();

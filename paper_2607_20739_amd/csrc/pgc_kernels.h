@@ -115,37 +115,19 @@ hipError_t launch_reduce_code(const ReduceCodeArgs& a, hipStream_t s);
 constexpr int kMlpMaxClasses = 16;
 constexpr int kMlpMaxHidden = 1024;
 
-// bf16 copies of the weights for the GEMMs: W1T[hidden][kpad] (kpad a multiple
-// of 64; zero past d_in),
+// bf16 copies of the weights for the GEMMs.  W1F: for each slice ks of 32
+// features (kslices = ceil(d_in / 32), zero past d_in) and tile ht of 16 hidden
+// units one MFMA fragment of 1 KiB, element (32 ks + 8 g + j, 16 ht + i) at
+//   W1F[((ks * hidden / 16 + ht) * 64 + 16 g + i) * 8 + j];
 // W2T[16][hidden] and W2p[hidden][16] (zero past `classes`).
 struct MlpCastArgs {
   const float* w;
-  __bf16* W1T;
+  __bf16* W1F;
   __bf16* W2T;
   __bf16* W2p;
-  int32_t d_in, kpad, hidden, classes;
+  int32_t d_in, kslices, hidden, classes;
 };
 hipError_t launch_mlp_cast(const MlpCastArgs& a, hipStream_t s);
-
-// H layout, blocked by 16 rows x 128 hidden units in the order of the head's
-// MFMA fragments: element (r, h) of evaluated partition e, with r = 16 rb + i
-// and h = 128 hb + 32 s + 8 g + j, at
-//   H[((((e * m_pad / 16 + rb) * hidden / 128 + hb) * 4 + s) * 64 + 16 g + i) * 8 + j].
-// A (16-row, 128-unit) block is 4 KiB of contiguous memory, and for each s the
-// 64 lanes of a head wave read 1 KiB of it in lane order.
-
-// H(e; r, h) = bf16(relu(X[k*m + r] . W1[:, h] + b1[h])) for each evaluated
-// partition k = e * part_stride + part_offset, e < n_eval, r < m, in the
-// blocked layout above; rows m .. m_pad - 1 are written as zeros.
-struct MlpForwardArgs {
-  const __bf16* X;
-  const __bf16* W1T;
-  const float* b1;
-  __bf16* H;
-  int64_t m, m_pad;
-  int32_t d_in, kpad, hidden, n_eval, part_stride, part_offset;
-};
-hipError_t launch_mlp_forward(const MlpForwardArgs& a, hipStream_t s);
 
 // dZ1 layout, blocked by 16 rows: element (r, h) of evaluated partition e at
 // dZ1[((e * m_pad / 16 + r / 16) * hidden + h) * 16 + r % 16], r < m_pad (a
@@ -155,23 +137,36 @@ __host__ __device__ inline int64_t mlp_dz1_index(int64_t m_pad, int32_t hidden, 
   return ((static_cast<int64_t>(e) * (m_pad / 16) + r / 16) * hidden + h) * 16 + r % 16;
 }
 
-// Per 16-row tile: logits, softmax, dZ2 = (p - onehot(y)) / m, dZ1 = (dZ2 W2^T)
-// masked by H > 0, written to dZ1 in the blocked layout above.  Each block writes partial sums of dW2^T[16][hidden], db1[hidden]
-// and db2[16] to partials[(e * blocks_per_part + b) * pstride].
-struct MlpHeadArgs {
-  const __bf16* H;
+// For each evaluated partition k = e * part_stride + part_offset, e < n_eval:
+// H = bf16(relu(X W1 + b1)) of its rows, logits, softmax, dZ2 = (p - onehot(y)) / m,
+// and dZ1 = (dZ2 W2^T) masked by H > 0, written in the blocked layout above
+// (rows m .. m_pad - 1 as zeros).  The partitions' tiles_per_part row tiles are
+// counted through and `blocks` blocks take an equal run of them each; block b
+// writes the sums over its rows of partition e to partials[(b + e) * pstride]:
+// dW2^T[16][hidden] in MFMA order (class 4 g + j of unit 16 ht + i at
+// ((ht * 4 + g) * 16 + i) * 4 + j; classes past the last group of four unwritten),
+// db1[hidden], db2[16].
+struct MlpRowsArgs {
+  const __bf16* X;
   const int32_t* y;
+  const __bf16* W1F;
   const __bf16* W2T;
   const __bf16* W2p;
+  const float* b1;
   const float* b2;
   __bf16* dZ1;
   float* partials;
-  int64_t m, m_pad, rows_per_block;
+  int64_t m, m_pad, pstride;
   float inv_m;
-  int32_t hidden, classes, blocks_per_part, n_eval, part_stride, part_offset, pstride;
+  int32_t d_in, kslices, classes, n_eval, blocks, part_stride, part_offset;
 };
-int mlp_head_threads(int hidden);
-hipError_t launch_mlp_head(const MlpHeadArgs& a, hipStream_t s);
+struct MlpRowsGrid {
+  int64_t tiles_per_part = 0;
+  int32_t blocks = 0;
+  int shape = 0;
+};
+MlpRowsGrid mlp_rows_grid(int64_t m_pad, int32_t n_eval, int32_t kslices, int32_t hidden);
+hipError_t launch_mlp_rows(const MlpRowsArgs& a, int32_t hidden, int shape, hipStream_t s);
 
 // dW1[i][h] = sum_r X[k*m + r][i] dZ1(e; r, h), written into the ring slot of
 // partition k: ring[((plane * n + k) * ld) + i * hidden + h].
@@ -184,14 +179,13 @@ struct MlpWgradArgs {
 };
 hipError_t launch_mlp_wgrad(const MlpWgradArgs& a, hipStream_t s);
 
-// Fold the head partials of each evaluated partition (fp64, block order) into
-// the b1, W2 and b2 parts of its ring slot.
+// Fold the rows kernel's sums of each evaluated partition (fp64, block order)
+// into the b1, W2 and b2 parts of its ring slot.
 struct MlpReduceArgs {
   const float* partials;
   float* ring;
-  int64_t ld;
-  int32_t d_in, hidden, classes, n, plane, n_eval, blocks_per_part, part_stride, part_offset,
-      pstride;
+  int64_t ld, tiles_per_part, pstride;
+  int32_t d_in, hidden, classes, n, plane, n_eval, blocks, part_stride, part_offset;
 };
 hipError_t launch_mlp_reduce(const MlpReduceArgs& a, hipStream_t s);
 

@@ -3,21 +3,21 @@
 // every worker evaluates one partition per step, Sec. IV-A / V-B).
 //
 // Per step, for the evaluated partitions:
-//   cast     w (fp32) -> W1T, W2T, W2p (bf16 copies laid out for the MFMAs)
-//   forward  H = relu(X W1 + b1)                       MFMA 16x16x32, tiles loaded
-//            straight into swizzled LDS, XCD-aware tile order
-//   head     logits = H W2 + b2, softmax, dZ2 = (p - onehot) / m,
+//   cast     w (fp32) -> W1F, W2T, W2p (bf16 copies laid out for the MFMAs)
+//   rows     H = relu(X W1 + b1), kept in registers     MFMA 16x16x32; then
+//            logits = H W2 + b2, softmax, dZ2 = (p - onehot) / m,
 //            dZ1 = (dZ2 W2^T) * [H > 0] (16-row blocked), and block
-//            partials of dW2 = H^T dZ2, db1, db2         MFMA 16x16x32 / 16x16x16
+//            partials of dW2 = H^T dZ2, db1, db2         MFMA 16x16x16
 //   wgrad    dW1 = X^T dZ1 straight into the ring slot  MFMA 16x16x32, both tiles
 //            loaded straight into LDS, X fragments by transposing LDS reads
-//   reduce   head partials -> b1, W2, b2 parts of the ring slot (fp64, fixed order)
+//   reduce   rows partials -> b1, W2, b2 parts of the ring slot (fp64, fixed order)
 //
 // MFMA lane layouts (gfx950, wave64; l = lane, lr = l % 16, lg = l / 16):
 //   16x16x32 bf16: A[lr][8 lg + j], B[8 lg + j][lr], j < 8;  D[4 lg + i][lr]
 //   16x16x16 bf16: A[lr][4 lg + j], B[4 lg + j][lr], j < 4;  D[4 lg + i][lr]
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <type_traits>
 
@@ -31,6 +31,7 @@ typedef __bf16 bf16;
 typedef bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef bf16 bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 
 __device__ __forceinline__ f32x4 mfma_k32(bf16x8 a, bf16x8 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, c, 0, 0, 0);
@@ -43,63 +44,35 @@ template <class T>
 __device__ __forceinline__ T load_vec(const bf16* p) { return *reinterpret_cast<const T*>(p); }
 
 // ---------------------------------------------------------------------------
-// cast
+// cast: W1 and W2 in bf16, in the order in which the rows kernel reads them.
+// One thread per 16 bytes of W1F (its loads are 64-byte pieces of W1's rows),
+// then one per element of the two W2 tables.
 // ---------------------------------------------------------------------------
 
 __global__ __launch_bounds__(256)
-void mlp_cast_w1_kernel(MlpCastArgs a) {
-  __shared__ float tile[32][33];
-  const int i0 = blockIdx.x * 32, h0 = blockIdx.y * 32;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
-  for (int j = ty; j < 32; j += 8) {
-    const int i = i0 + j;
-    tile[j][tx] = i < a.d_in ? a.w[static_cast<int64_t>(i) * a.hidden + h0 + tx] : 0.0f;
+void mlp_cast_kernel(MlpCastArgs a) {
+  const int htiles = a.hidden / 16;
+  const int64_t w1_items = static_cast<int64_t>(a.kslices) * htiles * 64;
+  const int64_t id = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+  if (id < w1_items) {
+    const int lane = static_cast<int>(id % 64);
+    const int64_t frag = id / 64;
+    const int h = static_cast<int>(frag % htiles) * 16 + (lane & 15);
+    const int64_t k0 = frag / htiles * 32 + (lane >> 4) * 8;
+    bf16x8 v;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) v[j] = static_cast<bf16>(k0 + j < a.d_in ? a.w[(k0 + j) * a.hidden + h] : 0.0f);
+    *reinterpret_cast<bf16x8*>(a.W1F + id * 8) = v;
+    return;
   }
-  __syncthreads();
-  for (int j = ty; j < 32; j += 8)
-    a.W1T[static_cast<int64_t>(h0 + j) * a.kpad + i0 + tx] = static_cast<bf16>(tile[tx][j]);
-}
-
-__global__ __launch_bounds__(256)
-void mlp_cast_w2_kernel(MlpCastArgs a) {
-  const int idx = blockIdx.x * 256 + threadIdx.x;
-  if (idx >= a.hidden * kMlpMaxClasses) return;
-  const int h = idx / kMlpMaxClasses, c = idx % kMlpMaxClasses;
+  const int64_t idx = id - w1_items;
+  if (idx >= static_cast<int64_t>(a.hidden) * kMlpMaxClasses) return;
+  const int h = static_cast<int>(idx / kMlpMaxClasses), c = static_cast<int>(idx % kMlpMaxClasses);
   const int64_t w2 = static_cast<int64_t>(a.d_in) * a.hidden + a.hidden;
   const float v = c < a.classes ? a.w[w2 + static_cast<int64_t>(h) * a.classes + c] : 0.0f;
   a.W2T[static_cast<int64_t>(c) * a.hidden + h] = static_cast<bf16>(v);
   a.W2p[idx] = static_cast<bf16>(v);
 }
-
-// ---------------------------------------------------------------------------
-// forward: H = relu(X W1 + b1).  Block tile BM samples x 256 hidden, K step
-// 64, 8 waves as WH (hidden) x WS (samples), one block per CU.  With BM = 384
-// the waves are 2 x 4 of 128 hidden x 96 samples (192 fp32 accumulators per
-// lane) and a K step's two tiles fill the 160 KiB of LDS in two buffers: per
-// MFMA FLOP a quarter fewer fragment reads and a sixth fewer tile bytes than a
-// 256 x 256 tile, and a third fewer blocks to start and drain.  Tiles travel
-// from global memory straight into LDS (16 bytes per lane, no register
-// staging), loaded one K step ahead: one barrier per K step.  In a tile row of
-// 64 bf16 (eight 16-byte chunks) chunk ch of row r sits at slot
-// ch ^ (r & 7) ^ ((r >> 3) & 1), so the 16 rows of a fragment read spread over
-// the slots.  The MFMAs produce H^T (A = W1^T rows, B = X rows), which leaves four
-// consecutive hidden units of one sample in each lane.  Block ids are mapped
-// so that all hidden tiles of a row tile run on the same XCD (workgroups are
-// dealt to the 8 XCDs round-robin) and share its L2.
-// ---------------------------------------------------------------------------
-
-constexpr int kFwBN = 256, kFwBK = 64, kFwStages = 2;
-constexpr int kFwThreads = 512;
-constexpr int kFwCpr = kFwBK / 8;                   // 16-byte chunks per tile row
-constexpr int kFwLdsBytes = 160 * 1024;
-constexpr int kXcds = 8;
-
-// Wave grid (hidden x samples) and epilogue passes per block tile height.
-// 256 x 256 tiles (4 x 2 waves of 64 x 128, one epilogue pass) measured 7%
-// slower than 384 x 256 on the 784 -> 1024 workload, with bitwise the same H.
-template <int BM> struct FwShape;
-template <> struct FwShape<384> { static constexpr int WH = 2, WS = 4, PASSES = 2; };
-constexpr int kFwBM = 384;   // samples per block tile
 
 typedef __attribute__((address_space(3))) void lds_void;
 typedef __attribute__((address_space(1))) void global_void;
@@ -109,15 +82,20 @@ __device__ __forceinline__ void load_lds16(const void* src, void* lds_wave_base)
   __builtin_amdgcn_global_load_lds((global_void*)src, (lds_void*)lds_wave_base, 16, 0, 0);
 }
 
-// Swizzle of a tile row's 16-byte chunks: chunk ch of row r sits at slot
-// ch ^ fw_swizzle(r).  It depends only on the row within its 16-row group, so a
-// lane's fragment reads for successive 16-row groups are a constant stride
-// apart, and rows r and r + 8 of a group land in different slots.
-__device__ __forceinline__ int fw_swizzle(int row) { return (row & 7) ^ ((row >> 3) & 1); }
-
 // 16 bytes from a wave-uniform base plus a per-lane byte offset to LDS.
 __device__ __forceinline__ void load_lds16_at(const bf16* base, uint32_t offset_bytes, void* lds_wave_base) {
   load_lds16(reinterpret_cast<const char*>(base) + offset_bytes, lds_wave_base);
+}
+
+// The same from a wave-uniform base plus a per-lane byte offset to a wave-uniform
+// LDS address, unknown to the compiler's wait insertion: before plain LDS reads
+// that follow the builtin it waits for every outstanding load of this kind (it
+// cannot tell the buffers apart), which would drain the prefetch.  The caller
+// orders the loads with wait_vmcnt and barriers; the compiler's own counted waits
+// only get stricter by loads that it does not count.
+__device__ __forceinline__ void load_lds16_async(const void* base, uint32_t offset_bytes, uint32_t lds_wave_base) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
+               :: "v"(offset_bytes), "s"(base), "s"(lds_wave_base) : "memory", "m0");
 }
 
 // Workgroup barrier that orders LDS only: the wave's own LDS reads and writes
@@ -140,352 +118,378 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt(0x0F70 | n);
 }
 
-template <int BM>
-__global__ __launch_bounds__(kFwThreads, 1)
-void mlp_forward_kernel(MlpForwardArgs a) {
-  using S = FwShape<BM>;
-  constexpr int kTH = kFwBN / S::WH, kTS = BM / S::WS;   // wave tile: hidden x samples
-  constexpr int kNT = kTH / 16, kMT = kTS / 16;
-  constexpr int kXTile = BM * kFwBK, kWTile = kFwBN * kFwBK;   // bf16 per operand tile
-  constexpr int kStage = kXTile + kWTile;
-  constexpr int kXRounds = kXTile / 8 / kFwThreads, kWRounds = kWTile / 8 / kFwThreads;
-  constexpr int kPassRows = BM / S::PASSES;   // output rows staged through LDS at a time
-  static_assert(S::WH * S::WS * 64 == kFwThreads && kTH % 16 == 0 && kTS % 16 == 0, "wave grid");
-  static_assert(kFwStages == 2, "one K step in flight: every load is waited for at the next barrier");
-  static_assert(kFwStages * kStage * 2 <= kFwLdsBytes, "LDS");
-  static_assert(kPassRows * kFwBN * 2 <= kFwStages * kStage * 2 && kPassRows % 16 == 0, "output staging");
-  static_assert(S::WS % S::PASSES == 0, "each pass stages whole sample groups");
-  __shared__ __attribute__((aligned(16))) bf16 smem[kFwStages * kStage];   // per buffer: X tile, W1^T tile
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int lr = lane & 15, lg = lane >> 4;
-  const int wh = wave % S::WH, ws = wave / S::WH;
+constexpr int kXcds = 8;
 
-  const int htiles = a.hidden / kFwBN;
-  const int64_t tiles_per_part = (a.m + BM - 1) / BM;
-  const int64_t rtiles = tiles_per_part * a.n_eval;
-  const int64_t id = blockIdx.x;
-  const int64_t rest = id / kXcds;
-  const int ht = static_cast<int>(rest % htiles);
-  const int64_t rt = (rest / htiles) * kXcds + id % kXcds;
-  if (rt >= rtiles) return;
-  const int e = static_cast<int>(rt / tiles_per_part);
-  const int64_t r0 = (rt % tiles_per_part) * BM;
-  const int h0 = ht * kFwBN;
-  const int64_t part = static_cast<int64_t>(e) * a.part_stride + a.part_offset;
-  const bf16* Xp = a.X + part * a.m * a.d_in;
-  const int ksteps = a.kpad / kFwBK;
-  const int dchunks = a.d_in / 8;
+typedef bf16 bf16x4v __attribute__((ext_vector_type(4)));
+typedef __attribute__((address_space(3))) bf16x4v lds_bf16x4;
 
-  // Chunk c = u * 512 + tid of a tile is row c / 8 = u * 64 + tid / 8 at slot
-  // c % 8 = tid % 8, which holds logical chunk (tid % 8) ^ swizzle(row); the
-  // swizzle does not change when 64 is added to the row, so the chunk is the
-  // same in every round.  Addresses are 32-bit byte offsets from the tile's
-  // first row (wave-uniform bases).  Rows past the partition read its last
-  // row, chunks past d_in read the row's first chunk: both are finite values
-  // that meet zero weights or land in rows that are never stored.
-  const int chunk = (tid & 7) ^ fw_swizzle(tid >> 3);
-  const bf16* Xt = Xp + r0 * a.d_in;
-  const int last_row = static_cast<int>(min<int64_t>(BM, a.m - r0)) - 1;
-  uint32_t xrow[kXRounds];
-#pragma unroll
-  for (int u = 0; u < kXRounds; ++u)
-    xrow[u] = static_cast<uint32_t>(min(u * 64 + (tid >> 3), last_row)) * static_cast<uint32_t>(a.d_in) * 2u;
-  const bf16* Wt = a.W1T + static_cast<int64_t>(h0) * a.kpad;
-  const uint32_t wrow = static_cast<uint32_t>(tid >> 3) * static_cast<uint32_t>(a.kpad) * 2u;
-  // The last K step covers columns kpad - 64 .. kpad - 1.  When its second
-  // half lies wholly past d_in (784 features: 800 .. 831), that half is
-  // neither loaded nor multiplied: its products with the zero W1^T columns
-  // are exact zeros.
-  const bool half_last = a.kpad - 32 >= a.d_in;
-  auto issue = [&](int ks, int buf, bool skip_upper) {
-    const int kc = ks * kFwCpr + chunk;
-    if (skip_upper && chunk >= kFwCpr / 2) return;
-    const uint32_t xk = static_cast<uint32_t>(kc < dchunks ? kc : 0) * 16u;
-#pragma unroll
-    for (int u = 0; u < kXRounds; ++u)
-      load_lds16_at(Xt, xrow[u] + xk, &smem[buf * kStage + (u * kFwThreads + wave * 64) * 8]);
-#pragma unroll
-    for (int u = 0; u < kWRounds; ++u)
-      load_lds16_at(Wt + static_cast<int64_t>(u * 64) * a.kpad, wrow + static_cast<uint32_t>(kc) * 16u,
-                    &smem[buf * kStage + kXTile + (u * kFwThreads + wave * 64) * 8]);
-  };
+__device__ __forceinline__ uint32_t lds_address(const bf16* p) {
+  return static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_bf16x4*)p));
+}
 
-  f32x4 acc[kNT][kMT];   // [hidden tile][sample tile], D = H^T
-#pragma unroll
-  for (int nt = 0; nt < kNT; ++nt)
-#pragma unroll
-    for (int mt = 0; mt < kMT; ++mt) acc[nt][mt] = f32x4{};
-  // A lane reads rows ws * kTS + mt * 16 + lr of the X tile and
-  // wh * kTH + nt * 16 + lr of the W1^T tile, chunk kk * 4 + lg of each.
-  const int lane_swz = fw_swizzle(lr);
-  // MFMAs over 32-column halves [K0, K1) of the K step held in buffer buf.
-  auto compute = [&](int buf, auto k0, auto k1) {
-    const bf16* Xs = smem + buf * kStage + (ws * kTS + lr) * kFwBK;
-    const bf16* Ws = smem + buf * kStage + kXTile + (wh * kTH + lr) * kFwBK;
-#pragma unroll
-    for (int kk = decltype(k0)::value; kk < decltype(k1)::value; ++kk) {
-      const int slot = ((kk * 4 + lg) ^ lane_swz) << 3;
-      bf16x8 xf[kMT];
-#pragma unroll
-      for (int mt = 0; mt < kMT; ++mt) xf[mt] = *reinterpret_cast<const bf16x8*>(Xs + mt * 16 * kFwBK + slot);
-#pragma unroll
-      for (int nt = 0; nt < kNT; ++nt) {
-        const bf16x8 wf = *reinterpret_cast<const bf16x8*>(Ws + nt * 16 * kFwBK + slot);
-#pragma unroll
-        for (int mt = 0; mt < kMT; ++mt) acc[nt][mt] = mfma_k32(wf, xf[mt], acc[nt][mt]);
-      }
-    }
-  };
-
-  using H0 = std::integral_constant<int, 0>;
-  using H1 = std::integral_constant<int, 1>;
-  using H2 = std::integral_constant<int, 2>;
-  static_assert(kFwBK == 64, "two 32-column halves per K step");
-  issue(0, 0, ksteps == 1 && half_last);
-  for (int ks = 0; ks + 1 < ksteps; ++ks) {
-    // This wave's loads of step ks have landed; after the barrier every
-    // wave's have, and every wave is done reading buffer (ks + 1) % 2, which
-    // the loads of step ks + 1 then overwrite.
-    wait_vmcnt<0>();
-    lds_barrier();
-    issue(ks + 1, (ks + 1) % kFwStages, ks + 2 == ksteps && half_last);
-    compute(ks % kFwStages, H0{}, H2{});
-  }
-  wait_vmcnt<0>();
-  lds_barrier();
-  compute((ksteps - 1) % kFwStages, H0{}, H1{});
-  if (!half_last) compute((ksteps - 1) % kFwStages, H1{}, H2{});
-
-  // Epilogue: bias and ReLU, then the tile goes through LDS, kPassRows rows at
-  // a time (row r's 16-byte chunk cc at slot cc ^ (r & 31)), so that H leaves
-  // in its blocked layout, 1 KiB of contiguous memory per store instruction.
-  lds_barrier();   // every wave is done reading the operand buffers
-  bf16* out = smem;
-  const int64_t hblocks = a.hidden / 128;
-  bf16* Hb = a.H + ((static_cast<int64_t>(e) * (a.m_pad / 16) + r0 / 16) * hblocks + h0 / 128) * 2048;
-  constexpr int kGroupsPerPass = S::WS / S::PASSES;
-#pragma unroll
-  for (int p = 0; p < S::PASSES; ++p) {
-    if (ws / kGroupsPerPass == p) {
-#pragma unroll
-      for (int nt = 0; nt < kNT; ++nt) {
-        const int hl = wh * kTH + nt * 16 + lg * 4;   // hidden column within the tile
-        float bias[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) bias[i] = a.b1[h0 + hl + i];
-#pragma unroll
-        for (int mt = 0; mt < kMT; ++mt) {
-          const int r = (ws % kGroupsPerPass) * kTS + mt * 16 + lr;   // row within the pass
-          bf16x4 v;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) v[i] = static_cast<bf16>(fmaxf(acc[nt][mt][i] + bias[i], 0.0f));
-          *reinterpret_cast<bf16x4*>(&out[r * kFwBN + (((hl >> 3) ^ (r & 31)) << 3) + (hl & 4)]) = v;
-        }
-      }
-    }
-    lds_barrier();
-    // The pass is kPassRows / 16 row blocks x 2 hidden blocks of 4 KiB; chunk
-    // q of a block is fragment slice q / 64, lane q % 64 (row q % 16, 8-unit
-    // group (q / 16) % 4).
-#pragma unroll 4
-    for (int it = 0; it < kPassRows * kFwBN / 8 / kFwThreads; ++it) {
-      const int q = it * kFwThreads + tid;
-      const int blk = q >> 8, rbl = blk >> 1, hbl = blk & 1, within = q & 255;
-      const int r = rbl * 16 + (within & 15);
-      const int cc = hbl * 16 + (within >> 6) * 4 + ((within >> 4) & 3);
-      const int64_t row = r0 + p * kPassRows + r;
-      if (row < a.m_pad) {
-        const bf16x8 v = row < a.m ? *reinterpret_cast<const bf16x8*>(&out[r * kFwBN + ((cc ^ (r & 31)) << 3)])
-                                   : bf16x8{};
-        // H (2 GB per step) cannot stay in the caches until the head reads it:
-        // streaming stores keep it from evicting the reused X and W1^T tiles.
-        __builtin_nontemporal_store(
-            v, reinterpret_cast<bf16x8*>(Hb + ((p * kPassRows / 16 + rbl) * hblocks + hbl) * 2048 + within * 8));
-      }
-    }
-    if (p + 1 < S::PASSES) lds_barrier();   // the next pass overwrites the staging area
+// NT transposing 8-byte LDS reads, 32 bytes apart, and the wait for them.  One
+// block of inline assembly: for the builtin the compiler waits for every
+// outstanding direct-to-LDS load and store first (it cannot tell the buffers
+// apart).  The memory clobber keeps it behind the LDS writes it reads.
+template <int NT>
+__device__ __forceinline__ void read_tr16(uint32_t addr, bf16x4v* v) {
+  static_assert(NT == 2 || NT == 4 || NT == 6 || NT == 8, "reads");
+  if constexpr (NT == 2) {
+    asm volatile("ds_read_b64_tr_b16 %0, %2\n\tds_read_b64_tr_b16 %1, %2 offset:32\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]) : "v"(addr) : "memory");
+  } else if constexpr (NT == 4) {
+    asm volatile("ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %4 offset:32\n\t"
+                 "ds_read_b64_tr_b16 %2, %4 offset:64\n\tds_read_b64_tr_b16 %3, %4 offset:96\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]) : "v"(addr) : "memory");
+  } else if constexpr (NT == 6) {
+    asm volatile("ds_read_b64_tr_b16 %0, %6\n\tds_read_b64_tr_b16 %1, %6 offset:32\n\t"
+                 "ds_read_b64_tr_b16 %2, %6 offset:64\n\tds_read_b64_tr_b16 %3, %6 offset:96\n\t"
+                 "ds_read_b64_tr_b16 %4, %6 offset:128\n\tds_read_b64_tr_b16 %5, %6 offset:160\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5])
+                 : "v"(addr) : "memory");
+  } else {
+    asm volatile("ds_read_b64_tr_b16 %0, %8\n\tds_read_b64_tr_b16 %1, %8 offset:32\n\t"
+                 "ds_read_b64_tr_b16 %2, %8 offset:64\n\tds_read_b64_tr_b16 %3, %8 offset:96\n\t"
+                 "ds_read_b64_tr_b16 %4, %8 offset:128\n\tds_read_b64_tr_b16 %5, %8 offset:160\n\t"
+                 "ds_read_b64_tr_b16 %6, %8 offset:192\n\tds_read_b64_tr_b16 %7, %8 offset:224\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&v"(v[0]), "=&v"(v[1]), "=&v"(v[2]), "=&v"(v[3]), "=&v"(v[4]), "=&v"(v[5]), "=&v"(v[6]),
+                   "=&v"(v[7])
+                 : "v"(addr) : "memory");
   }
 }
 
 // ---------------------------------------------------------------------------
-// head: one wave per 128 hidden columns, 16-row tiles.  The wave's partial
-// logits are summed across waves through LDS in wave order (one barrier per
-// tile).  Each wave stages its 16 x 128 tile of H through its own LDS area,
-// from which each lane reads the four rows of one hidden unit that
-// serve as the ReLU mask and the dW2 operand.  dH comes out of the MFMA as
-// four consecutive rows of one hidden unit per lane, which is dZ1's 16-row
-// blocked layout: the tile's dZ1 leaves straight from registers, a contiguous
-// 512-byte run per store.
+// rows: forward, softmax and the backward pass down to dZ1 in one kernel, so
+// that H never leaves the chip.  A block of 8 waves holds BM = 16 MT rows by
+// all hidden units in accumulators (wave w: units 16 NT w ..), and walks an
+// equal run of the evaluated partitions' row tiles.
+//   H^T = relu(W1^T X^T + b1), K slices of 32 columns.
+//     W1F comes from L2 in fragment order, each wave's fragments into a ring of
+//     WB slices of its own in LDS: no barrier and no swizzle, the wave waits for
+//     its own loads.  X rows, shared by the waves, go through WB + 1 stages
+//     (64-byte rows; chunk ch of row r at slot ch ^ (r >> 1 & 3), so that any 8
+//     rows of a fragment read cover the banks), one barrier per slice.  W1F's
+//     slice s + WB - 1 and X's slice s + WB are issued at slice s.
+//   logits^T = W2^T H^T: the MFMA result H^T is the next one's B operand as it
+//     stands, so the logits come straight from registers.  The waves' partial
+//     logits meet in LDS; wave w does the softmax of 16-row tiles w, w + 8, ..
+//     and leaves dZ2 there, both ways round.
+//   dH = dZ2 W2^T, masked by H > 0, is dZ1; dW2^T += dZ2^T H.  Both want H with
+//     its rows in the registers: each wave turns its 16 x 16 NT tiles through its
+//     own part of the ring (transposing LDS reads).
+// The next tile's first slices are loaded while the softmax runs, and have
+// landed before the first dZ1 store is issued, so no wait of the next tile
+// includes the stores of this one before a whole slice has passed.
+// Bound by the loads of W1F and by the slices' barriers: 1,048,576 rows of
+// 784 -> 1024 -> 10 take 2.33 ms (0.67 ms of MFMAs; 1.62 ms without the loads),
+// against 1.94 + 0.78 ms for a forward kernel that writes H and a head that reads it.
 // ---------------------------------------------------------------------------
 
-constexpr int kHeadCols = 128;
-constexpr int kHeadMaxWaves = kMlpMaxHidden / kHeadCols;
-constexpr int kHtLd = kHeadCols + 16;  // H tile row stride (bf16): 288 bytes, so the four
-                                       // 32-byte row pieces of a transposing read hit
-                                       // distinct banks
+constexpr int kRowsThreads = 512, kRowsWaves = 8;
 
-typedef bf16 bf16x4t __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) bf16x4t lds_bf16x4t;
-
-__global__ __launch_bounds__(64 * kHeadMaxWaves)
-void mlp_head_kernel(MlpHeadArgs a) {
-  __shared__ float zpart[2][kHeadMaxWaves][16][16];
-  __shared__ float dzt[kHeadMaxWaves][16][17];
-  __shared__ bf16 Ht[kHeadMaxWaves][16][kHtLd];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+template <int NT, int MT, int WB>
+__global__ __launch_bounds__(kRowsThreads, 1)
+void mlp_rows_kernel(MlpRowsArgs a) {
+  constexpr int kBM = 16 * MT, kHidden = 16 * NT * kRowsWaves;
+  constexpr int kD = WB, kStages = WB + 1;              // X slices in flight, stages
+  constexpr int kXStage = kBM * 32;                     // bf16
+  constexpr int kWSlice = NT * 512;                     // bf16 per wave
+  constexpr int kXLanes = 8 * MT;                       // 16-byte chunks of an X slice per wave
+  constexpr int kTrLd = 16 * NT + 16;                   // row stride of the transposing area (bf16): the row
+                                                        // pieces of a read hit distinct banks
+  // Loads issued after W1F's slice s when it is waited for: those of slices 1 ..
+  // WB - 2 go out together before slice 0 (at least kFirstInFlight), later ones
+  // one slice at a time with a slice of X each.
+  constexpr int kInFlight = 1 + (WB - 2) * (NT + 1), kFirstInFlight = 1 + (WB - 2) * NT;
+  static_assert(MT <= 8 && WB >= 2, "one X load per lane and slice");
+  static_assert(MT * 1024 <= (WB - 1) * kWSlice * 2 && 16 * kTrLd <= (WB - 1) * kWSlice,
+                "the ring past its first slice holds the partial logits, then the transposing area");
+  __shared__ __attribute__((aligned(16))) bf16 xs[kStages * kXStage];
+  __shared__ __attribute__((aligned(16))) bf16 ring[kRowsWaves * WB * kWSlice];
+  __shared__ __attribute__((aligned(16))) bf16 dzs[MT][2][256];   // dZ2 [row][class], [class][row]
+  __shared__ float db2s[kRowsWaves][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int lr = lane & 15, lg = lane >> 4;
-  const int waves = a.hidden / kHeadCols;
-  const int e = blockIdx.y;
-  const int64_t part = static_cast<int64_t>(e) * a.part_stride + a.part_offset;
-  const int hw0 = wave * kHeadCols;
-  const int64_t hidden = a.hidden;
-  // This wave's 4 KiB block of H for row block rb starts at Hw + rb * hblocks * 2048.
-  const int64_t hblocks = hidden / 128;
-  const bf16* Hw = a.H + (static_cast<int64_t>(e) * (a.m_pad / 16) * hblocks + wave) * 2048;
-  const int32_t* yp = a.y + part * a.m;
-  bf16* dz1 = a.dZ1 + mlp_dz1_index(a.m_pad, a.hidden, e, 0, 0);
-  const int64_t rbeg = static_cast<int64_t>(blockIdx.x) * a.rows_per_block;
-  const int64_t rend = min(rbeg + a.rows_per_block, a.m_pad);
+  const int h0 = wave * 16 * NT;
+  bf16* const mine = ring + wave * (WB * kWSlice);
+  bf16* const area = mine + kWSlice;
+  const uint32_t xs_at = lds_address(xs);
+  const uint32_t mine_at = lds_address(ring) + static_cast<uint32_t>(wave * (WB * kWSlice * 2));
 
-  bf16x8 w2t[4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) w2t[ks] = load_vec<bf16x8>(a.W2T + lr * hidden + hw0 + ks * 32 + lg * 8);
-  bf16x4 w2p[8];
-#pragma unroll
-  for (int ht = 0; ht < 8; ++ht) w2p[ht] = load_vec<bf16x4>(a.W2p + (hw0 + ht * 16 + lr) * 16 + lg * 4);
-  const float b2 = lr < a.classes ? a.b2[lr] : 0.0f;
+  const int64_t tiles_per_part = (a.m_pad + kBM - 1) / kBM;
+  const int64_t tiles = tiles_per_part * a.n_eval;
+  int64_t t = linear_block_row(tiles, a.blocks, blockIdx.x);
+  const int64_t t_end = linear_block_row(tiles, a.blocks, blockIdx.x + int64_t{1});
+  const int kslices = a.kslices;
+  const int dchunks = a.d_in / 8;
 
-  f32x4 dw2[8];
-  float db1[8];   // this lane's rows' share of db1[hw0 + 16 ht + lr]
-#pragma unroll
-  for (int ht = 0; ht < 8; ++ht) {
-    dw2[ht] = f32x4{};
-    db1[ht] = 0.0f;
-  }
-  float db2 = 0.0f;
-  int buf = 0;
-  // H fragments of the logits GEMM (row r0 + lr, columns hw0 + 32 ks + 8 lg ..)
-  // and the labels of rows r0 + 4 lg + i, fetched two tiles ahead into two
-  // alternating register sets (labels loaded later would make every wait for
-  // them wait for the prefetched tiles too: loads complete in order).
-  bf16x8 ha[4], hb[4];
-  int la[4], lb[4];
-  // Every fetch issues the same loads on every path (H rows m .. m_pad - 1 are
-  // zeros; labels past the partition read its last row), and the values are
-  // only masked where a tile uses them, so the compiler's waits for a register
-  // set count exactly the loads issued after it.  Slice ks of the block is
-  // 1 KiB in lane order: row r0 + lr, columns hw0 + 32 ks + 8 lg .. + 7.
-  auto fetch_h = [&](int64_t r0, bf16x8* dst, int* lab) {
-    const bf16* blk = Hw + (r0 / 16) * hblocks * 2048;
-#pragma unroll
-    for (int ks = 0; ks < 4; ++ks) dst[ks] = load_vec<bf16x8>(blk + ks * 512 + lane * 8);
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int64_t lrow = r0 + lg * 4 + i;
-      lab[i] = yp[lrow < a.m ? lrow : a.m - 1];
-    }
+  // This lane's chunk of every X slice: row xrow of the tile, chunk xch.
+  const int xrow = wave * 2 * MT + (lane >> 2);
+  const int xch = (lane & 3) ^ ((xrow >> 1) & 3);
+  auto tile_base = [&](int64_t tile, int64_t* r0) {
+    const int64_t e = tile / tiles_per_part;
+    *r0 = tile % tiles_per_part * kBM;
+    return a.X + ((e * a.part_stride + a.part_offset) * a.m + min(*r0, a.m - 1)) * a.d_in;
   };
-  auto tile = [&](int64_t r0, bf16x8* hcur, int* lcur) {
-    f32x4 z = f32x4{};
-    const bool hrow = r0 + lr < a.m;
+  // Rows past the partition read its last row, chunks past d_in the row's
+  // first chunk: values of that row, which meet zero weights or a zero dZ2.
+  auto x_offset = [&](int64_t r0) {
+    const int last_row = static_cast<int>(max<int64_t>(min<int64_t>(kBM, a.m - r0), 1)) - 1;
+    return static_cast<uint32_t>(min(xrow, last_row)) * static_cast<uint32_t>(a.d_in) * 2u;
+  };
+  auto issue_x = [&](const bf16* Xt, uint32_t row_offset, int s, int stage) {
+    const int kc = s * 4 + xch;
+    if (lane < kXLanes)
+      load_lds16_async(Xt, row_offset + static_cast<uint32_t>(kc < dchunks ? kc : 0) * 16u,
+                       xs_at + static_cast<uint32_t>((stage * kXStage + wave * (2 * MT * 32)) * 2));
+  };
+  // Byte offsets into W1F fit 32 bits (hidden * 32 kslices * 2 <= 2^31 + 2^16).
+  const uint32_t wlane = static_cast<uint32_t>(wave * NT * 1024 + lane * 16);
+  auto issue_w = [&](int s, int buf) {
+    uint32_t at = wlane + static_cast<uint32_t>(s) * (kHidden * 64u);
+    asm volatile("" : "+v"(at));   // computed here, not kept from tile to tile
+    const uint32_t dst = mine_at + static_cast<uint32_t>(buf * kWSlice * 2);
 #pragma unroll
-    for (int ks = 0; ks < 4; ++ks) {
-      const bf16x8 hv = hrow ? hcur[ks] : bf16x8{};
-      z = mfma_k32(hv, w2t[ks], z);
-      *reinterpret_cast<bf16x8*>(&Ht[wave][lr][ks * 32 + lg * 8]) = hv;
+    for (int nt = 0; nt < NT; ++nt) load_lds16_async(a.W1F, at + nt * 1024u, dst + nt * 1024u);
+  };
+
+  if (lane < 16) db2s[wave][lane] = 0.0f;
+  int64_t r0;
+  const bf16* Xt = tile_base(t, &r0);
+  uint32_t xoff = x_offset(r0);
+  issue_w(0, 0);
+#pragma unroll
+  for (int s = 0; s < kD; ++s)
+    if (s < kslices) issue_x(Xt, xoff, s, s);
+  wait_vmcnt<0>();
+  lds_barrier();
+
+  int64_t run_e = -1;   // partition of the sums in this block's current slot
+  for (; t < t_end; ++t) {
+    const int64_t e = t / tiles_per_part;
+    const bool fresh = e != run_e;
+    run_e = e;
+
+    f32x4 acc[NT][MT];
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt)
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = f32x4{};
+    const int slot = (lg ^ ((lr >> 1) & 3)) << 3;
+    auto compute = [&](int stage, int buf) {
+      const bf16* Xs = xs + stage * kXStage + lr * 32 + slot;
+      const bf16* Ws = mine + buf * kWSlice + lane * 8;
+      if constexpr (MT <= NT) {
+        bf16x8 xf[MT];
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) xf[mt] = load_vec<bf16x8>(Xs + mt * 512);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const bf16x8 wf = load_vec<bf16x8>(Ws + nt * 512);
+#pragma unroll
+          for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = mfma_k32(wf, xf[mt], acc[nt][mt]);
+        }
+      } else {
+        bf16x8 wf[NT];
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) wf[nt] = load_vec<bf16x8>(Ws + nt * 512);
+#pragma unroll
+        for (int mt = 0; mt < MT; ++mt) {
+          const bf16x8 xf = load_vec<bf16x8>(Xs + mt * 512);
+#pragma unroll
+          for (int nt = 0; nt < NT; ++nt) acc[nt][mt] = mfma_k32(wf[nt], xf, acc[nt][mt]);
+        }
+      }
+    };
+
+    // Slice 0 of W1F and the first kD slices of X are in LDS.
+#pragma unroll
+    for (int s = 1; s + 1 < WB; ++s)
+      if (s < kslices) issue_w(s, s);
+    int stage = 0, buf = 0;   // of slice s; the ones before it are free
+    for (int s = 0; s < kslices; ++s) {
+      if (s + WB - 1 < kslices) issue_w(s + WB - 1, buf == 0 ? WB - 1 : buf - 1);
+      if (s + kD < kslices) issue_x(Xt, xoff, s + kD, stage == 0 ? kStages - 1 : stage - 1);
+      compute(stage, buf);
+      stage = stage + 1 == kStages ? 0 : stage + 1;
+      buf = buf + 1 == WB ? 0 : buf + 1;
+      const int next = s + 1;
+      if (next < kslices) {
+        // Everything but the loads issued after W1F's slice `next` has landed,
+        // X's before it; near the end, where fewer were issued, everything.
+        if (next + kD > kslices) wait_vmcnt<0>();
+        else if (WB > 2 && next < WB - 1) wait_vmcnt<kFirstInFlight>();
+        else wait_vmcnt<kInFlight>();
+        lds_barrier();
+      }
     }
-    int label[4];
+
+    // Lane indices of what follows, opaque so that no address made from them
+    // is kept in registers through the K loop.
+    int lr_ = lr, lg_ = lg;
+    asm volatile("" : "+v"(lr_), "+v"(lg_));
+    // H^T in bf16, and this wave's part of the logits (class 4 lg + i, row lr).
+    bf16x4 hb[NT][MT];
+    f32x4 z[MT];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) label[i] = r0 + lg * 4 + i < a.m ? lcur[i] : -1;
-    // The last two tiles of the block refetch themselves; the values go unused.
-    fetch_h(r0 + 32 < rend ? r0 + 32 : r0, hcur, lcur);
+    for (int nt = 0; nt < NT; ++nt) {
+      float bias[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) zpart[buf][wave][lg * 4 + i][lr] = z[i];
-    // LDS-only barrier: the H prefetch and the dZ1 stores stay in flight.
-    lds_barrier();
-    // Softmax over the classes of rows r0 + 4 lg + i (class lr on this lane).
-    float dz2[4];
+      for (int i = 0; i < 4; ++i) bias[i] = a.b1[h0 + nt * 16 + 4 * lg_ + i];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      float s = 0.0f;
-      for (int w = 0; w < waves; ++w) s += zpart[buf][w][lg * 4 + i][lr];
-      const int64_t row = r0 + lg * 4 + i;
-      const bool live = lr < a.classes;
-      const float v = live ? s + b2 : -INFINITY;
-      const float mx = row16_max(v);
-      const float ex = live ? expf(v - mx) : 0.0f;
-      const float sum = row16_sum(ex);
-      dz2[i] = (row < a.m && live) ? (ex / sum - (lr == label[i] ? 1.0f : 0.0f)) * a.inv_m : 0.0f;
-      db2 += dz2[i];
-    }
-    buf ^= 1;
-    // The transposes below go through this wave's private LDS areas; a wave's
-    // LDS operations complete in order, so they need no barrier.
+      for (int mt = 0; mt < MT; ++mt) {
+        bf16x4 v;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) dzt[wave][lg * 4 + i][lr] = dz2[i];
-    bf16x4 dz_b, dz_a;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      dz_b[j] = static_cast<bf16>(dzt[wave][lr][lg * 4 + j]);   // dZ2[r0 + lr][4 lg + j]
-      dz_a[j] = static_cast<bf16>(dz2[j]);                     // dZ2[r0 + 4 lg + j][lr]
+        for (int i = 0; i < 4; ++i) v[i] = static_cast<bf16>(fmaxf(acc[nt][mt][i] + bias[i], 0.0f));
+        // Packed at once: two registers follow the four accumulators.
+        u32x2 packed = __builtin_bit_cast(u32x2, v);
+        asm volatile("" : "+v"(packed));
+        hb[nt][mt] = __builtin_bit_cast(bf16x4, packed);
+      }
     }
 #pragma unroll
-    for (int ht = 0; ht < 8; ++ht) {
-      const int h = ht * 16;   // within the wave's columns
-      // H[r0 + 4 lg + j][hw0 + h + lr]: the ReLU mask of dH below and the B
-      // operand of dW2.
-      // One transposing read: within each 16-lane group, lane i receives
-      // element i % 4 of the 4-element row pieces addressed by lanes 4 j + i / 4,
-      // so lane q addresses row 4 lg + q / 4, columns h + 4 (q % 4) .. + 3.
-      const bf16x4t ht4 = __builtin_amdgcn_ds_read_tr16_b64_v4bf16(
-          (lds_bf16x4t*)&Ht[wave][lg * 4 + (lr >> 2)][h + 4 * (lr & 3)]);
-      const bf16x4 hcol = {ht4[0], ht4[1], ht4[2], ht4[3]};
-      // dH[r0 + 4 lg + i][hw0 + h + lr] = sum_c dZ2[r0 + 4 lg + i][c] W2[hw0 + h + lr][c]
-      // (A = dZ2 rows, B = W2^T columns: the lane's four values are four
-      // consecutive rows of one hidden unit, 8 contiguous bytes of dZ1's
-      // 16-row blocked layout).
-      const f32x4 dh = mfma_k16(dz_b, w2p[ht], f32x4{});
-      bf16x4 g4;
-      float gsum = 0.0f;
+    for (int mt = 0; mt < MT; ++mt) z[mt] = f32x4{};
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      const bf16x4 w2t = load_vec<bf16x4>(a.W2T + lr_ * kHidden + h0 + nt * 16 + 4 * lg_);
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) z[mt] = mfma_k16(w2t, hb[nt][mt], z[mt]);
+    }
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) *reinterpret_cast<f32x4*>(area + mt * 512 + (lg_ * 16 + lr_) * 8) = z[mt];
+    lds_barrier();   // the partial logits are there, and every wave is done with the X stages
+
+    const int64_t this_r0 = r0;
+    if (t + 1 < t_end) {
+      Xt = tile_base(t + 1, &r0);
+      xoff = x_offset(r0);
+      issue_w(0, 0);
+#pragma unroll
+      for (int s = 0; s < kD; ++s)
+        if (s < kslices) issue_x(Xt, xoff, s, s);
+    }
+
+    const int64_t part = e * a.part_stride + a.part_offset;
+    if (wave < MT) {   // MT <= 8: one tile per wave
+      const int64_t row = this_r0 + wave * 16 + lr_;
+      const int label = a.y[part * a.m + min(row, a.m - 1)];
+      float b2[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) b2[i] = a.b2[min(4 * lg_ + i, a.classes - 1)];
+      f32x4 v = f32x4{};
+#pragma unroll
+      for (int w = 0; w < kRowsWaves; ++w)
+        v += *reinterpret_cast<const f32x4*>(ring + w * (WB * kWSlice) + kWSlice + wave * 512 + (lg_ * 16 + lr_) * 8);
+      float mx = -INFINITY;
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const float g = static_cast<float>(hcol[i]) > 0.0f ? dh[i] : 0.0f;
-        gsum += g;
-        g4[i] = static_cast<bf16>(g);
+        v[i] = 4 * lg_ + i < a.classes ? v[i] + b2[i] : -INFINITY;
+        mx = fmaxf(mx, v[i]);
       }
-      db1[ht] += gsum;
-      // The 64 lanes write one contiguous 512-byte run of the dZ1 block.
-      *reinterpret_cast<bf16x4*>(dz1 + ((r0 / 16) * hidden + hw0 + h + lr) * 16 + lg * 4) = g4;
-      // dW2^T[4 lg + i][h + lr] += sum_r dZ2[r][4 lg + i] H[r][h + lr]
-      dw2[ht] = mfma_k16(dz_a, hcol, dw2[ht]);
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      float ex[4], sum = 0.0f;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        ex[i] = expf(v[i] - mx);   // 0 past the classes
+        sum += ex[i];
+      }
+      sum += __shfl_xor(sum, 16, 64);
+      sum += __shfl_xor(sum, 32, 64);
+      bf16x4 dz;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int c = 4 * lg_ + i;
+        const float g =
+            (row < a.m && c < a.classes) ? (ex[i] / sum - (c == label ? 1.0f : 0.0f)) * a.inv_m : 0.0f;
+        dz[i] = static_cast<bf16>(g);
+        dzs[wave][1][c * 16 + lr_] = dz[i];
+        const float s = row16_sum(g);
+        if (lr_ == 0) db2s[wave][c] += s;
+      }
+      *reinterpret_cast<bf16x4*>(&dzs[wave][0][lr_ * 16 + 4 * lg_]) = dz;
     }
-  };
-  // A block covers a multiple of 64 rows (head grid), so tiles come in pairs.
-  if (rbeg < rend) {
-    fetch_h(rbeg, ha, la);
-    fetch_h(rbeg + 16, hb, lb);
-  }
-  for (int64_t r0 = rbeg; r0 < rend; r0 += 32) {
-    tile(r0, ha, la);
-    tile(r0 + 16, hb, lb);
-  }
+    wait_vmcnt<0>();   // the next tile's first slices, ahead of this tile's stores
+    lds_barrier();
 
-  float* out = a.partials + (static_cast<int64_t>(e) * a.blocks_per_part + blockIdx.x) * a.pstride;
+    // The slot's sums so far (dW2^T: class 4 lg + i, unit h0 + 16 nt + lr).
+    float* const out = a.partials + (blockIdx.x + e) * a.pstride;
+    f32x4* const out_w2 = reinterpret_cast<f32x4*>(out) + wave * NT * 64 + lg_ * 16 + lr_;
+    float* const out_b1 = out + kMlpMaxClasses * kHidden + h0 + lr_;
+    const bool classes_here = 4 * lg_ < a.classes;
+    f32x4 dw2[NT];
+    float db1[NT];
+    bf16x4 w2p[NT];
 #pragma unroll
-  for (int ht = 0; ht < 8; ++ht) {
-    const int h = hw0 + ht * 16;
+    for (int nt = 0; nt < NT; ++nt) {
+      dw2[nt] = f32x4{};
+      db1[nt] = 0.0f;
+      w2p[nt] = load_vec<bf16x4>(a.W2p + (h0 + nt * 16 + lr_) * kMlpMaxClasses + 4 * lg_);
+    }
+    if (!fresh) {   // classes past the last group of four: never stored
 #pragma unroll
-    for (int i = 0; i < 4; ++i) out[(lg * 4 + i) * hidden + h + lr] = dw2[ht][i];
-    float s = db1[ht];
-    s += __shfl_xor(s, 16, 64);
-    s += __shfl_xor(s, 32, 64);
-    if (lg == 0) out[kMlpMaxClasses * hidden + h + lr] = s;
-  }
-  if (wave == 0) {
-    float s = db2;
-    s += __shfl_xor(s, 16, 64);
-    s += __shfl_xor(s, 32, 64);
-    if (lane < 16) out[(kMlpMaxClasses + 1) * hidden + lane] = s;
+      for (int nt = 0; nt < NT; ++nt) dw2[nt] = out_w2[nt * 64];
+    }
+    bf16* const dz1 = a.dZ1 + mlp_dz1_index(a.m_pad, kHidden, static_cast<int32_t>(e), this_r0, h0);
+    const uint32_t tr = lds_address(area + (4 * lg_ + (lr_ >> 2)) * kTrLd + 4 * (lr_ & 3));
+#pragma unroll
+    for (int mt = 0; mt < MT; ++mt) {
+      if (this_r0 + mt * 16 < a.m_pad) {
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt)
+          *reinterpret_cast<bf16x4*>(area + lr_ * kTrLd + nt * 16 + 4 * lg_) = hb[nt][mt];
+        const bf16x4 dz_b = load_vec<bf16x4>(&dzs[mt][0][lr_ * 16 + 4 * lg_]);   // dZ2[lr][4 lg + j]
+        const bf16x4 dz_a = load_vec<bf16x4>(&dzs[mt][1][lr_ * 16 + 4 * lg_]);   // dZ2[4 lg + j][lr]
+        // H[row 4 lg + j][h0 + 16 nt + lr]: within each 16-lane group, lane i
+        // receives element i % 4 of the row pieces addressed by lanes 4 j + i / 4.
+        bf16x4v hv[NT];
+        read_tr16<NT>(tr, hv);
+#pragma unroll
+        for (int nt = 0; nt < NT; ++nt) {
+          const bf16x4 hcol = {hv[nt][0], hv[nt][1], hv[nt][2], hv[nt][3]};
+          // dH[row 4 lg + i][unit lr]: four consecutive rows of one unit, 8
+          // contiguous bytes of dZ1's layout; a wave's store is a 512-byte run.
+          const f32x4 dh = mfma_k16(dz_b, w2p[nt], f32x4{});
+          bf16x4 g4;
+          float gsum = 0.0f;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            const float g = static_cast<float>(hcol[i]) > 0.0f ? dh[i] : 0.0f;
+            gsum += g;
+            g4[i] = static_cast<bf16>(g);
+          }
+          db1[nt] += gsum;
+          // dZ1 is streamed: it should not push W1F out of the L2.
+          __builtin_nontemporal_store(g4, reinterpret_cast<bf16x4*>(
+              dz1 + (static_cast<int64_t>(mt) * kHidden + nt * 16 + lr_) * 16 + 4 * lg_));
+          dw2[nt] = mfma_k16(dz_a, hcol, dw2[nt]);
+        }
+      }
+    }
+#pragma unroll
+    for (int nt = 0; nt < NT; ++nt) {
+      if (classes_here) out_w2[nt * 64] = dw2[nt];
+      float s = db1[nt];
+      s += __shfl_xor(s, 16, 64);
+      s += __shfl_xor(s, 32, 64);
+      if (lg_ == 0) out_b1[nt * 16] = fresh ? s : out_b1[nt * 16] + s;
+    }
+    // Every wave has added its tiles' dZ2 (the barrier above): at the end of the
+    // block's rows of a partition, their sum goes to the slot.
+    if (t + 1 == t_end || (t + 1) / tiles_per_part != e) {
+      if (wave == 0 && lane < 16) {
+        float s = 0.0f;
+#pragma unroll
+        for (int w = 0; w < kRowsWaves; ++w) {
+          s += db2s[w][lane];
+          db2s[w][lane] = 0.0f;
+        }
+        out[(kMlpMaxClasses + 1) * kHidden + lane] = s;
+      }
+    }
   }
 }
 
@@ -519,9 +523,6 @@ constexpr int kWgStageBytes = (kWgAChunks + kWgBChunks) * 16;
 constexpr int kWgALoads = kWgAChunks / kWgThreads, kWgBLoads = kWgBChunks / kWgThreads;
 static_assert(kWgALoads * kWgThreads == kWgAChunks && kWgBLoads * kWgThreads == kWgBChunks, "load rounds");
 static_assert(kWgStages * kWgStageBytes <= 160 * 1024, "LDS");
-
-typedef bf16 bf16x4v __attribute__((ext_vector_type(4)));
-typedef __attribute__((address_space(3))) bf16x4v lds_bf16x4;
 
 __device__ __forceinline__ int wg_half_swizzle(int h) { return ((h >> 2) ^ (h >> 3)) & 1; }
 __device__ __forceinline__ int wg_row_swizzle(int r) { return 2 * ((r & 3) | (((r >> 3) & 1) << 2)); }
@@ -670,55 +671,96 @@ void mlp_wgrad_kernel(MlpWgradArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// reduce: head partials -> ring (b1, W2 in [hidden][classes] order, b2)
+// reduce: rows partials -> ring (b1, W2 in [hidden][classes] order, b2)
 // ---------------------------------------------------------------------------
 
 __global__ __launch_bounds__(256)
 void mlp_reduce_kernel(MlpReduceArgs a) {
   const int j = blockIdx.x * 256 + threadIdx.x;
   if (j >= a.pstride) return;
-  const int e = blockIdx.y;
-  const int64_t part = static_cast<int64_t>(e) * a.part_stride + a.part_offset;
-  const float* p = a.partials + static_cast<int64_t>(e) * a.blocks_per_part * a.pstride + j;
-  double s = 0.0;
-  for (int b = 0; b < a.blocks_per_part; ++b) s += static_cast<double>(p[static_cast<int64_t>(b) * a.pstride]);
-  float* slot = a.ring + (static_cast<int64_t>(a.plane) * a.n + part) * a.ld;
   const int64_t w1 = static_cast<int64_t>(a.d_in) * a.hidden;
   const int hw = kMlpMaxClasses * a.hidden;
-  if (j < hw) {
-    const int c = j / a.hidden, h = j % a.hidden;
-    if (c < a.classes) slot[w1 + a.hidden + static_cast<int64_t>(h) * a.classes + c] = static_cast<float>(s);
+  int64_t at;
+  if (j < hw) {   // dW2^T in MFMA order: 16 units x 16 classes, four classes of one unit together
+    const int c = 4 * (j / 64 % 4) + j % 4, h = j / 256 * 16 + j / 4 % 16;
+    if (c >= a.classes) return;
+    at = w1 + a.hidden + static_cast<int64_t>(h) * a.classes + c;
   } else if (j < hw + a.hidden) {
-    slot[w1 + (j - hw)] = static_cast<float>(s);
+    at = w1 + (j - hw);
   } else {
     const int c = j - hw - a.hidden;
-    if (c < a.classes)
-      slot[w1 + a.hidden + static_cast<int64_t>(a.hidden) * a.classes + c] = static_cast<float>(s);
+    if (c >= a.classes) return;
+    at = w1 + a.hidden + static_cast<int64_t>(a.hidden) * a.classes + c;
   }
+  const int64_t e = blockIdx.y;
+  const int64_t part = e * a.part_stride + a.part_offset;
+  const int64_t tiles = a.tiles_per_part * a.n_eval;
+  const int64_t first = linear_row_block(tiles, a.blocks, e * a.tiles_per_part);
+  const int64_t last = linear_row_block(tiles, a.blocks, (e + 1) * a.tiles_per_part - 1);
+  const float* p = a.partials + (first + e) * a.pstride + j;
+  const int count = static_cast<int>(last - first) + 1;
+  double s = 0.0;
+  int b = 0;
+  for (; b + 8 <= count; b += 8) {
+    float v[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) v[i] = p[static_cast<int64_t>(b + i) * a.pstride];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) s += static_cast<double>(v[i]);
+  }
+  for (; b < count; ++b) s += static_cast<double>(p[static_cast<int64_t>(b) * a.pstride]);
+  a.ring[(static_cast<int64_t>(a.plane) * a.n + part) * a.ld + at] = static_cast<float>(s);
 }
+
+// Row tiles of the rows kernel by hidden / 256 - 1: MT (16-row groups per tile)
+// and the ring's slices, largest tile first.
+using RowsKernel = void (*)(MlpRowsArgs);
+struct RowsShape { int mt; RowsKernel kernel; };
+constexpr int kRowsShapes = 3;
+const RowsShape kRows[4][kRowsShapes] = {
+    {{6, mlp_rows_kernel<2, 6, 4>}, {4, mlp_rows_kernel<2, 4, 4>}, {2, mlp_rows_kernel<2, 2, 4>}},
+    {{8, mlp_rows_kernel<4, 8, 3>}, {4, mlp_rows_kernel<4, 4, 3>}, {2, mlp_rows_kernel<4, 2, 3>}},
+    {{6, mlp_rows_kernel<6, 6, 2>}, {4, mlp_rows_kernel<6, 4, 2>}, {2, mlp_rows_kernel<6, 2, 2>}},
+    {{6, mlp_rows_kernel<8, 6, 2>}, {4, mlp_rows_kernel<8, 4, 2>}, {2, mlp_rows_kernel<8, 2, 2>}}};
+constexpr int kRowsBlocks = 256;   // one per CU
 
 }  // namespace
 
+// The tile that ends first by this estimate of a block's time, in clocks: per K
+// slice the MFMAs of its two waves per SIMD or the slice's W1F bytes from L2 at
+// 44 bytes per clock, whichever takes longer, then the softmax and dZ1.
+MlpRowsGrid mlp_rows_grid(int64_t m_pad, int32_t n_eval, int32_t kslices, int32_t hidden) {
+  const int nt = hidden / 128;
+  MlpRowsGrid best;
+  double best_cost = 0.0;
+  for (int i = 0; i < kRowsShapes; ++i) {
+    const int mt = kRows[hidden / 256 - 1][i].mt;
+    MlpRowsGrid g;
+    g.shape = i;
+    g.tiles_per_part = (m_pad + 16 * mt - 1) / (16 * mt);
+    const int64_t tiles = g.tiles_per_part * n_eval;
+    g.blocks = static_cast<int32_t>(std::min<int64_t>(kRowsBlocks, tiles));
+    const double slice = std::max(32.0 * nt * mt, (nt * 8192.0 + mt * 1024.0) / 44.0) + 200.0;
+    const double cost =
+        static_cast<double>((tiles + g.blocks - 1) / g.blocks) * (kslices * slice + 270.0 * nt * mt + 6000.0);
+    if (i == 0 || cost < best_cost) {
+      best = g;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 hipError_t launch_mlp_cast(const MlpCastArgs& a, hipStream_t s) {
-  hipLaunchKernelGGL(mlp_cast_w1_kernel, dim3(a.kpad / 32, a.hidden / 32), dim3(256), 0, s, a);
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(mlp_cast_w2_kernel, dim3((a.hidden * kMlpMaxClasses + 255) / 256), dim3(256), 0, s, a);
+  const int64_t items = static_cast<int64_t>(a.kslices) * a.hidden * 4 + static_cast<int64_t>(a.hidden) * kMlpMaxClasses;
+  hipLaunchKernelGGL(mlp_cast_kernel, dim3(static_cast<unsigned>((items + 255) / 256)), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_forward(const MlpForwardArgs& a, hipStream_t s) {
-  const int64_t rtiles = (a.m + kFwBM - 1) / kFwBM * a.n_eval;
-  dim3 grid(static_cast<unsigned>((rtiles + kXcds - 1) / kXcds * kXcds * (a.hidden / kFwBN)));
-  hipLaunchKernelGGL(mlp_forward_kernel<kFwBM>, grid, dim3(kFwThreads), 0, s, a);
-  return hipGetLastError();
-}
-
-int mlp_head_threads(int hidden) { return 64 * (hidden / kHeadCols); }
-
-hipError_t launch_mlp_head(const MlpHeadArgs& a, hipStream_t s) {
-  dim3 grid(a.blocks_per_part, a.n_eval);
-  hipLaunchKernelGGL(mlp_head_kernel, grid, dim3(mlp_head_threads(a.hidden)), 0, s, a);
+hipError_t launch_mlp_rows(const MlpRowsArgs& a, int32_t hidden, int shape, hipStream_t s) {
+  if (hidden < 256 || hidden > kMlpMaxHidden || hidden % 256 != 0 || shape < 0 || shape >= kRowsShapes || a.blocks < 1)
+    return hipErrorInvalidValue;
+  hipLaunchKernelGGL(kRows[hidden / 256 - 1][shape].kernel, dim3(a.blocks), dim3(kRowsThreads), 0, s, a);
   return hipGetLastError();
 }
 

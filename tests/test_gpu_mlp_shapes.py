@@ -1,0 +1,56 @@
+"""The MLP gradient over the shapes at which its kernels change course: every row tile of the
+rows kernel at each hidden width (few, some and many rows), runs of tiles that cross
+partitions, tiles past a partition's rows, one and two K slices.
+
+Each part of every partition's gradient (dW1, db1, dW2, db2) is compared with the fp64 oracle
+on the ring after the first step.  H, dZ2 and dZ1 are rounded to bf16 (2^-9 of each term at
+most), so a part is off by a few 2^-9 of its largest entry where few rows are summed: the bf16
+bar of 2e-2 covers that.
+"""
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2607_20739_amd as P
+from oracle import pgc_oracle as O
+
+from _parity import normwise_error
+
+pytestmark = pytest.mark.gpu
+
+BF16_TOL = 2e-2
+
+# n, m, d_in, hidden, classes
+SHAPES = [
+    (4, 100, 64, 256, 10), (4, 3000, 8, 256, 3), (3, 20000, 40, 256, 16),
+    (3, 700, 264, 512, 5), (4, 3400, 200, 512, 16), (3, 22000, 72, 512, 10),
+    (3, 65, 24, 768, 1 + 1), (4, 3400, 96, 768, 9), (3, 15990, 40, 768, 4),
+    (4, 1000, 32, 1024, 13), (4, 3400, 784, 1024, 10), (3, 16100, 104, 1024, 10),
+    (5, 1, 16, 1024, 2), (130 // 2, 33, 48, 256, 7),
+]
+
+
+@pytest.mark.parametrize("n,m,d,hidden,classes", SHAPES)
+def test_partition_gradients_match_the_oracle(n, m, d, hidden, classes):
+    print("\n[gpu case] MLP n=%d m=%d %d-%d-%d" % (n, m, d, hidden, classes), flush=True)
+    q = d * hidden + hidden + hidden * classes + classes
+    g = torch.Generator().manual_seed(n + m + d + hidden)
+    X = torch.rand(n * m, d, generator=g).bfloat16()
+    y = torch.randint(classes, (n * m,), generator=g, dtype=torch.int32)
+    w = torch.randn(q, generator=g) * 0.1
+    sess = P.PGCSession("CR", n, 2, "mlp", n * m, d, hidden=hidden, classes=classes)
+    try:
+        wd = w.cuda()
+        sess.step(X.cuda(), y.cuda(), wd, np.zeros(n, np.uint8), 0.0)
+        assert torch.equal(wd.cpu(), w)
+        cuts = np.cumsum([d * hidden, hidden, hidden * classes])
+        for k in sorted({0, n // 2, n - 1}):
+            ref = O.partition_gradient(O.MLP, X[k * m:(k + 1) * m].double().numpy(), y[k * m:(k + 1) * m].numpy(),
+                                       w.double().numpy(), (d, hidden, classes))
+            got = sess.ring(k, 0).cpu().numpy()
+            errs = [normwise_error(a, b) for a, b in zip(np.split(got, cuts), np.split(ref, cuts))]
+            print("  partition %d: dW1 %.2g db1 %.2g dW2 %.2g db2 %.2g" % ((k,) + tuple(errs)), flush=True)
+            assert max(errs) <= BF16_TOL
+    finally:
+        sess.close()
