@@ -111,6 +111,18 @@ __device__ __forceinline__ void lds_barrier() {
   asm volatile("" ::: "memory");
 }
 
+// The wave's own LDS reads and writes complete.
+__device__ __forceinline__ void lds_wait() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt(0xC07F);
+  asm volatile("" ::: "memory");
+}
+
+// Swizzle of the 16-byte chunks of an X stage's 128-byte rows: chunk ch of row r
+// sits at slot ch ^ x_swizzle(r).  It depends on the row within its 16-row group,
+// and the rows of a fragment read spread over the slots.
+__device__ __forceinline__ int x_swizzle(int row) { return (row & 7) ^ ((row >> 3) & 1); }
+
 // s_waitcnt with vmcnt = n (n < 16) and the other counters left alone.
 template <int n>
 __device__ __forceinline__ void wait_vmcnt() {
@@ -169,10 +181,9 @@ __device__ __forceinline__ void read_tr16(uint32_t addr, bf16x4v* v) {
 //   H^T = relu(W1^T X^T + b1), K slices of 32 columns.
 //     W1F comes from L2 in fragment order, each wave's fragments into a ring of
 //     WB slices of its own in LDS: no barrier and no swizzle, the wave waits for
-//     its own loads.  X rows, shared by the waves, go through WB + 1 stages
-//     (64-byte rows; chunk ch of row r at slot ch ^ (r >> 1 & 3), so that any 8
-//     rows of a fragment read cover the banks), one barrier per slice.  W1F's
-//     slice s + WB - 1 and X's slice s + WB are issued at slice s.
+//     its own loads.  X rows, shared by the waves, go through two stages of two
+//     slices (swizzled 128-byte rows), one barrier per stage: within it the waves
+//     drift apart, and one's LDS reads run beside another's MFMAs.
 //   logits^T = W2^T H^T: the MFMA result H^T is the next one's B operand as it
 //     stands, so the logits come straight from registers.  The waves' partial
 //     logits meet in LDS; wave w does the softmax of 16-row tiles w, w + 8, ..
@@ -194,20 +205,18 @@ template <int NT, int MT, int WB>
 __global__ __launch_bounds__(kRowsThreads, 1)
 void mlp_rows_kernel(MlpRowsArgs a) {
   constexpr int kBM = 16 * MT, kHidden = 16 * NT * kRowsWaves;
-  constexpr int kD = WB, kStages = WB + 1;              // X slices in flight, stages
-  constexpr int kXStage = kBM * 32;                     // bf16
+  constexpr int kXStage = kBM * 64;                     // bf16: two K slices
   constexpr int kWSlice = NT * 512;                     // bf16 per wave
-  constexpr int kXLanes = 8 * MT;                       // 16-byte chunks of an X slice per wave
+  constexpr int kXLoads = (MT + 3) / 4;                 // X loads per lane and stage (16 MT chunks per wave)
   constexpr int kTrLd = 16 * NT + 16;                   // row stride of the transposing area (bf16): the row
                                                         // pieces of a read hit distinct banks
-  // Loads issued after W1F's slice s when it is waited for: those of slices 1 ..
-  // WB - 2 go out together before slice 0 (at least kFirstInFlight), later ones
-  // one slice at a time with a slice of X each.
-  constexpr int kInFlight = 1 + (WB - 2) * (NT + 1), kFirstInFlight = 1 + (WB - 2) * NT;
-  static_assert(MT <= 8 && WB >= 2, "one X load per lane and slice");
+  // Loads that may be outstanding when W1F's slice s is waited for.  After it came
+  // W1F's slices up to s + WB - 2 and, at odd s, X's next stage; at even s that
+  // stage is needed, and only one slice of W1F came after it.
+  constexpr int kOddInFlight = (WB - 2) * NT + kXLoads, kEvenInFlight = WB > 2 ? NT : 0;
   static_assert(MT * 1024 <= (WB - 1) * kWSlice * 2 && 16 * kTrLd <= (WB - 1) * kWSlice,
                 "the ring past its first slice holds the partial logits, then the transposing area");
-  __shared__ __attribute__((aligned(16))) bf16 xs[kStages * kXStage];
+  __shared__ __attribute__((aligned(16))) bf16 xs[2 * kXStage];
   __shared__ __attribute__((aligned(16))) bf16 ring[kRowsWaves * WB * kWSlice];
   __shared__ __attribute__((aligned(16))) bf16 dzs[MT][2][256];   // dZ2 [row][class], [class][row]
   __shared__ float db2s[kRowsWaves][16];
@@ -226,9 +235,9 @@ void mlp_rows_kernel(MlpRowsArgs a) {
   const int kslices = a.kslices;
   const int dchunks = a.d_in / 8;
 
-  // This lane's chunk of every X slice: row xrow of the tile, chunk xch.
-  const int xrow = wave * 2 * MT + (lane >> 2);
-  const int xch = (lane & 3) ^ ((xrow >> 1) & 3);
+  // This lane's chunks of every X stage: row xrow + 8 u of the tile, slot
+  // lane % 8, which holds chunk slot ^ x_swizzle(row).
+  const int xrow = wave * 2 * MT + (lane >> 3);
   auto tile_base = [&](int64_t tile, int64_t* r0) {
     const int64_t e = tile / tiles_per_part;
     *r0 = tile % tiles_per_part * kBM;
@@ -236,15 +245,20 @@ void mlp_rows_kernel(MlpRowsArgs a) {
   };
   // Rows past the partition read its last row, chunks past d_in the row's
   // first chunk: values of that row, which meet zero weights or a zero dZ2.
-  auto x_offset = [&](int64_t r0) {
+  auto x_rows = [&](int64_t r0, uint32_t* offset) {
     const int last_row = static_cast<int>(max<int64_t>(min<int64_t>(kBM, a.m - r0), 1)) - 1;
-    return static_cast<uint32_t>(min(xrow, last_row)) * static_cast<uint32_t>(a.d_in) * 2u;
+#pragma unroll
+    for (int u = 0; u < kXLoads; ++u)
+      offset[u] = static_cast<uint32_t>(min(xrow + 8 * u, last_row)) * static_cast<uint32_t>(a.d_in) * 2u;
   };
-  auto issue_x = [&](const bf16* Xt, uint32_t row_offset, int s, int stage) {
-    const int kc = s * 4 + xch;
-    if (lane < kXLanes)
-      load_lds16_async(Xt, row_offset + static_cast<uint32_t>(kc < dchunks ? kc : 0) * 16u,
-                       xs_at + static_cast<uint32_t>((stage * kXStage + wave * (2 * MT * 32)) * 2));
+  auto issue_x = [&](const bf16* Xt, const uint32_t* offset, int step, int stage) {
+#pragma unroll
+    for (int u = 0; u < kXLoads; ++u) {
+      const int kc = step * 8 + ((lane & 7) ^ x_swizzle(xrow + 8 * u));
+      if (u * 64 + lane < 16 * MT)
+        load_lds16_async(Xt, offset[u] + static_cast<uint32_t>(kc < dchunks ? kc : 0) * 16u,
+                         xs_at + static_cast<uint32_t>(stage * kXStage * 2 + (wave * 2 * MT + 8 * u) * 128));
+    }
   };
   // Byte offsets into W1F fit 32 bits (hidden * 32 kslices * 2 <= 2^31 + 2^16).
   const uint32_t wlane = static_cast<uint32_t>(wave * NT * 1024 + lane * 16);
@@ -259,11 +273,10 @@ void mlp_rows_kernel(MlpRowsArgs a) {
   if (lane < 16) db2s[wave][lane] = 0.0f;
   int64_t r0;
   const bf16* Xt = tile_base(t, &r0);
-  uint32_t xoff = x_offset(r0);
+  uint32_t xoff[kXLoads];
+  x_rows(r0, xoff);
   issue_w(0, 0);
-#pragma unroll
-  for (int s = 0; s < kD; ++s)
-    if (s < kslices) issue_x(Xt, xoff, s, s);
+  issue_x(Xt, xoff, 0, 0);
   wait_vmcnt<0>();
   lds_barrier();
 
@@ -275,17 +288,20 @@ void mlp_rows_kernel(MlpRowsArgs a) {
 
     f32x4 acc[NT][MT];
 #pragma unroll
-    for (int nt = 0; nt < NT; ++nt)
+    for (int nt = 0; nt < NT; ++nt) {   // H^T starts from its bias
+      f32x4 bias;
 #pragma unroll
-      for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = f32x4{};
-    const int slot = (lg ^ ((lr >> 1) & 3)) << 3;
-    auto compute = [&](int stage, int buf) {
-      const bf16* Xs = xs + stage * kXStage + lr * 32 + slot;
+      for (int i = 0; i < 4; ++i) bias[i] = a.b1[h0 + nt * 16 + 4 * lg + i];
+#pragma unroll
+      for (int mt = 0; mt < MT; ++mt) acc[nt][mt] = bias;
+    }
+    auto compute = [&](int stage, int half, int buf) {
+      const bf16* Xs = xs + stage * kXStage + lr * 64 + (((half * 4 + lg) ^ x_swizzle(lr)) << 3);
       const bf16* Ws = mine + buf * kWSlice + lane * 8;
       if constexpr (MT <= NT) {
         bf16x8 xf[MT];
 #pragma unroll
-        for (int mt = 0; mt < MT; ++mt) xf[mt] = load_vec<bf16x8>(Xs + mt * 512);
+        for (int mt = 0; mt < MT; ++mt) xf[mt] = load_vec<bf16x8>(Xs + mt * 1024);
 #pragma unroll
         for (int nt = 0; nt < NT; ++nt) {
           const bf16x8 wf = load_vec<bf16x8>(Ws + nt * 512);
@@ -298,32 +314,37 @@ void mlp_rows_kernel(MlpRowsArgs a) {
         for (int nt = 0; nt < NT; ++nt) wf[nt] = load_vec<bf16x8>(Ws + nt * 512);
 #pragma unroll
         for (int mt = 0; mt < MT; ++mt) {
-          const bf16x8 xf = load_vec<bf16x8>(Xs + mt * 512);
+          const bf16x8 xf = load_vec<bf16x8>(Xs + mt * 1024);
 #pragma unroll
           for (int nt = 0; nt < NT; ++nt) acc[nt][mt] = mfma_k32(wf[nt], xf, acc[nt][mt]);
         }
       }
     };
 
-    // Slice 0 of W1F and the first kD slices of X are in LDS.
+    // Slice 0 of W1F and the first stage of X are in LDS.
 #pragma unroll
     for (int s = 1; s + 1 < WB; ++s)
       if (s < kslices) issue_w(s, s);
-    int stage = 0, buf = 0;   // of slice s; the ones before it are free
-    for (int s = 0; s < kslices; ++s) {
-      if (s + WB - 1 < kslices) issue_w(s + WB - 1, buf == 0 ? WB - 1 : buf - 1);
-      if (s + kD < kslices) issue_x(Xt, xoff, s + kD, stage == 0 ? kStages - 1 : stage - 1);
-      compute(stage, buf);
-      stage = stage + 1 == kStages ? 0 : stage + 1;
-      buf = buf + 1 == WB ? 0 : buf + 1;
-      const int next = s + 1;
-      if (next < kslices) {
-        // Everything but the loads issued after W1F's slice `next` has landed,
-        // X's before it; near the end, where fewer were issued, everything.
-        if (next + kD > kslices) wait_vmcnt<0>();
-        else if (WB > 2 && next < WB - 1) wait_vmcnt<kFirstInFlight>();
-        else wait_vmcnt<kInFlight>();
+    int buf = 0;   // of slice s; the one before it is free
+    for (int s = 0; s < kslices; s += 2) {
+      const int stage = (s >> 1) & 1;
+      // Near the end, where fewer loads were issued, wait for all of them.
+      if (s > 0) {
+        if (s + max(WB - 2, 1) < kslices) wait_vmcnt<kEvenInFlight>();
+        else wait_vmcnt<0>();
         lds_barrier();
+      }
+      if (s + WB - 1 < kslices) issue_w(s + WB - 1, buf == 0 ? WB - 1 : buf - 1);
+      if (s + 2 < kslices) issue_x(Xt, xoff, (s >> 1) + 1, stage ^ 1);
+      compute(stage, 0, buf);
+      buf = buf + 1 == WB ? 0 : buf + 1;
+      if (s + 1 < kslices) {
+        if (s + 1 + max(WB - 2, 1) < kslices) wait_vmcnt<kOddInFlight>();
+        else wait_vmcnt<0>();
+        lds_wait();   // this wave's reads of the slice that is overwritten next
+        if (s + WB < kslices) issue_w(s + WB, buf == 0 ? WB - 1 : buf - 1);
+        compute(stage, 1, buf);
+        buf = buf + 1 == WB ? 0 : buf + 1;
       }
     }
 
@@ -336,14 +357,11 @@ void mlp_rows_kernel(MlpRowsArgs a) {
     f32x4 z[MT];
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt) {
-      float bias[4];
-#pragma unroll
-      for (int i = 0; i < 4; ++i) bias[i] = a.b1[h0 + nt * 16 + 4 * lg_ + i];
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
         bf16x4 v;
 #pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = static_cast<bf16>(fmaxf(acc[nt][mt][i] + bias[i], 0.0f));
+        for (int i = 0; i < 4; ++i) v[i] = static_cast<bf16>(fmaxf(acc[nt][mt][i], 0.0f));
         // Packed at once: two registers follow the four accumulators.
         u32x2 packed = __builtin_bit_cast(u32x2, v);
         asm volatile("" : "+v"(packed));
@@ -365,11 +383,9 @@ void mlp_rows_kernel(MlpRowsArgs a) {
     const int64_t this_r0 = r0;
     if (t + 1 < t_end) {
       Xt = tile_base(t + 1, &r0);
-      xoff = x_offset(r0);
+      x_rows(r0, xoff);
       issue_w(0, 0);
-#pragma unroll
-      for (int s = 0; s < kD; ++s)
-        if (s < kslices) issue_x(Xt, xoff, s, s);
+      issue_x(Xt, xoff, 0, 0);
     }
 
     const int64_t part = e * a.part_stride + a.part_offset;
