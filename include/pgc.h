@@ -73,7 +73,7 @@ enum pgc_mask_policy {
 /* Kernels whose GPU time pgc_kernel_time reports. */
 enum pgc_kernel {
   PGC_KERNEL_GRADIENT = 0,    /* linear models: per-partition gradient, one HBM pass over the rows */
-  PGC_KERNEL_REDUCE = 1,      /* MLP: head partial sums -> ring slots */
+  PGC_KERNEL_REDUCE = 1,      /* MLP: partial sums of the other kernels -> ring slots */
   PGC_KERNEL_CODE = 2,        /* encode + masked decode + update (linear models: also folds the
                                  gradient kernel's partial sums into the ring first) */
   PGC_KERNEL_MLP_CAST = 3,    /* MLP: bf16 copies of W1 and W2 */

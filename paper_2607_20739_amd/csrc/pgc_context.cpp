@@ -95,9 +95,10 @@ struct pgc_ctx {
   int64_t ld = 0;             // floats between ring slots / coded words
   LinearGrid warm, pipe;      // linear gradient grids
   pgc::MlpRowsGrid rows_warm, rows_pipe;   // MLP rows kernel grids
+  int splits_warm = 1, splits_pipe = 1;    // row splits of the MLP weight gradient
   int64_t kslices = 0, m_pad = 0, pstride = 0;
   size_t off_ring = 0, off_coded = 0, off_decoded = 0, off_partials = 0, off_coef = 0, ws_need = 0;
-  size_t off_w1f = 0, off_w2t = 0, off_w2p = 0, off_dz1 = 0;
+  size_t off_w1f = 0, off_w2t = 0, off_w2p = 0, off_dz1 = 0, off_splits = 0;
   size_t noalloc_bytes = 0;   // linear models: the partial sums pgc_step_noalloc accounts for
   char* ws = nullptr;
   size_t ws_bytes = 0;
@@ -161,6 +162,11 @@ void compute_layout(pgc_ctx* ctx) {
     ctx->off_w2p = take(2 * static_cast<size_t>(hidden * pgc::kMlpMaxClasses));
     ctx->off_dz1 = take(2 * static_cast<size_t>(n) * hidden * ctx->m_pad);
     ctx->off_partials = take(sizeof(float) * static_cast<size_t>(slots * ctx->pstride));
+    ctx->splits_warm = pgc::mlp_wgrad_splits(ctx->m_pad, n, ctx->cfg.d_in, static_cast<int32_t>(hidden));
+    ctx->splits_pipe = pgc::mlp_wgrad_splits(ctx->m_pad, n_pipe, ctx->cfg.d_in, static_cast<int32_t>(hidden));
+    const int64_t sums = std::max(ctx->splits_warm > 1 ? int64_t{ctx->splits_warm} * n : 0,
+                                  ctx->splits_pipe > 1 ? int64_t{ctx->splits_pipe} * n_pipe : 0);
+    ctx->off_splits = take(sizeof(float) * static_cast<size_t>(sums * ctx->cfg.d_in * hidden));
   } else {
     ctx->warm = make_linear_grid(ctx->m, n, q);
     ctx->pipe = make_linear_grid(ctx->m, n_pipe, q);
@@ -577,8 +583,9 @@ int linear_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc:
                       [&] { return pgc::launch_reduce_code(ra, ctx->stream); });
 }
 
-// a4-a5 for the MLP: cast, rows (forward to dZ1), weight gradient, small-part
-// reduce, then copies of the slot into the other planes at the CR warm-up.
+// a4-a5 for the MLP: cast, rows (forward to dZ1), weight gradient, reduce (small
+// parts and the sums of its row splits), then copies of the slot into the other
+// planes at the CR warm-up.
 int mlp_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc::Decode& dec, float lr,
              bool warm, int32_t n_eval, int32_t part_stride, int32_t part_offset, int plane_first, int plane_count) {
   const pgc::MlpRowsGrid& grid = warm ? ctx->rows_warm : ctx->rows_pipe;
@@ -627,21 +634,13 @@ int mlp_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc::De
   wg.n_eval = n_eval;
   wg.part_stride = part_stride;
   wg.part_offset = part_offset;
-  pgc::MlpReduceArgs rd{};
-  rd.partials = partials;
-  rd.ring = ring;
-  rd.ld = ctx->ld;
-  rd.d_in = d_in;
-  rd.hidden = hidden;
-  rd.classes = classes;
-  rd.n = ctx->n;
-  rd.plane = plane_first;
-  rd.n_eval = n_eval;
-  rd.tiles_per_part = grid.tiles_per_part;
-  rd.blocks = grid.blocks;
-  rd.part_stride = part_stride;
-  rd.part_offset = part_offset;
-  rd.pstride = ctx->pstride;
+  wg.splits = warm ? ctx->splits_warm : ctx->splits_pipe;
+  wg.split_sums = ws_ptr<float>(ctx, ctx->off_splits);
+  wg.small.partials = partials;
+  wg.small.tiles_per_part = grid.tiles_per_part;
+  wg.small.pstride = ctx->pstride;
+  wg.small.blocks = grid.blocks;
+  wg.small.classes = classes;
 
   int st = timed_launch(ctx, PGC_KERNEL_MLP_CAST, "MLP cast kernel",
                         [&] { return pgc::launch_mlp_cast(cast, ctx->stream); });
@@ -653,7 +652,7 @@ int mlp_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc::De
                       [&] { return pgc::launch_mlp_wgrad(wg, ctx->stream); });
   if (st == PGC_OK)
     st = timed_launch(ctx, PGC_KERNEL_REDUCE, "MLP reduce kernel", [&] {
-      hipError_t e = pgc::launch_mlp_reduce(rd, ctx->stream);
+      hipError_t e = pgc::launch_mlp_reduce(wg, ctx->stream);
       // CR warm-up: every plane holds the step-0 gradient of each partition.
       const size_t plane_bytes = sizeof(float) * static_cast<size_t>(ctx->n) * ctx->ld;
       for (int p = 1; p < plane_count && e == hipSuccess; ++p)

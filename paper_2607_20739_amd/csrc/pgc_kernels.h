@@ -168,26 +168,31 @@ struct MlpRowsGrid {
 MlpRowsGrid mlp_rows_grid(int64_t m_pad, int32_t n_eval, int32_t kslices, int32_t hidden);
 hipError_t launch_mlp_rows(const MlpRowsArgs& a, int32_t hidden, int shape, hipStream_t s);
 
+// The rows kernel's sums, as MlpRowsArgs describes them.
+struct MlpSmallParts {
+  const float* partials;
+  int64_t tiles_per_part, pstride;
+  int32_t blocks, classes;
+};
+
 // dW1[i][h] = sum_r X[k*m + r][i] dZ1(e; r, h), written into the ring slot of
-// partition k: ring[((plane * n + k) * ld) + i * hidden + h].
+// partition k: ring[((plane * n + k) * ld) + i * hidden + h].  With splits > 1 a
+// partition's rows are cut into that many equal runs of 64-row steps, whose sums go
+// to split_sums[(e * splits + split) * d_in * hidden + ..]; launch_mlp_reduce folds
+// them into the slots, and always writes the slots' b1, W2 and b2 parts from the rows
+// kernel's sums (fp64, fixed order).
 struct MlpWgradArgs {
   const __bf16* X;
   const __bf16* dZ1;
   float* ring;
+  float* split_sums;
+  MlpSmallParts small;
   int64_t m, m_pad, ld;
-  int32_t d_in, hidden, n, plane, n_eval, part_stride, part_offset;
+  int32_t d_in, hidden, n, plane, n_eval, splits, part_stride, part_offset;
 };
+int mlp_wgrad_splits(int64_t m_pad, int32_t n_eval, int32_t d_in, int32_t hidden);
 hipError_t launch_mlp_wgrad(const MlpWgradArgs& a, hipStream_t s);
-
-// Fold the rows kernel's sums of each evaluated partition (fp64, block order)
-// into the b1, W2 and b2 parts of its ring slot.
-struct MlpReduceArgs {
-  const float* partials;
-  float* ring;
-  int64_t ld, tiles_per_part, pstride;
-  int32_t d_in, hidden, classes, n, plane, n_eval, blocks, part_stride, part_offset;
-};
-hipError_t launch_mlp_reduce(const MlpReduceArgs& a, hipStream_t s);
+hipError_t launch_mlp_reduce(const MlpWgradArgs& a, hipStream_t s);
 
 // Header of a saved pipeline state: the first kStateHeaderBytes bytes of the
 // caller's buffer (the rest of the struct's space is zero), followed by the

@@ -9,8 +9,10 @@
 //            dZ1 = (dZ2 W2^T) * [H > 0] (16-row blocked), and block
 //            partials of dW2 = H^T dZ2, db1, db2         MFMA 16x16x16
 //   wgrad    dW1 = X^T dZ1 straight into the ring slot  MFMA 16x16x32, both tiles
-//            loaded straight into LDS, X fragments by transposing LDS reads
-//   reduce   rows partials -> b1, W2, b2 parts of the ring slot (fp64, fixed order)
+//            loaded straight into LDS, X fragments by transposing LDS reads; few
+//            partitions split their rows over several blocks
+//   reduce   rows partials -> b1, W2, b2 parts of the ring slot, and the sums of
+//            the weight gradient's splits (fp64, fixed order)
 //
 // MFMA lane layouts (gfx950, wave64; l = lane, lr = l % 16, lg = l / 16):
 //   16x16x32 bf16: A[lr][8 lg + j], B[8 lg + j][lr], j < 8;  D[4 lg + i][lr]
@@ -195,7 +197,7 @@ __device__ __forceinline__ void read_tr16(uint32_t addr, bf16x4v* v) {
 // landed before the first dZ1 store is issued, so no wait of the next tile
 // includes the stores of this one before a whole slice has passed.
 // Bound by the loads of W1F and by the slices' barriers: 1,048,576 rows of
-// 784 -> 1024 -> 10 take 2.33 ms (0.67 ms of MFMAs; 1.62 ms without the loads),
+// 784 -> 1024 -> 10 take 2.22 ms (0.67 ms of MFMAs; 1.51 ms without the loads),
 // against 1.94 + 0.78 ms for a forward kernel that writes H and a head that reads it.
 // ---------------------------------------------------------------------------
 
@@ -510,7 +512,7 @@ void mlp_rows_kernel(MlpRowsArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// wgrad: dW1^T = dZ1^T X per partition, block tile 256 hidden x 224 features,
+// wgrad: dW1^T = dZ1^T X per partition (or per split of its rows), block tile 256 hidden x 224 features,
 // K = rows in steps of 64.  8 waves: wave (wh, wf) owns hidden rows
 // 64 wh .. 64 wh + 63 and features 112 wf .. 112 wf + 111 of the tile (a wave
 // whose features all lie past d_in skips its MFMAs).  Both operands travel
@@ -554,35 +556,44 @@ __device__ __forceinline__ bf16x4v ds_read_tr16(const bf16* p) {
   return v;
 }
 
+// The ring slot that evaluated partition e's gradient goes to.
+__device__ __forceinline__ float* ring_slot(const MlpWgradArgs& a, int64_t e) {
+  return a.ring + (static_cast<int64_t>(a.plane) * a.n + e * a.part_stride + a.part_offset) * a.ld;
+}
+
 __global__ __launch_bounds__(kWgThreads, 1)
 void mlp_wgrad_kernel(MlpWgradArgs a) {
   __shared__ __attribute__((aligned(16))) unsigned char smem[kWgStages * kWgStageBytes];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int lr = lane & 15, lg = lane >> 4;
   const int wh = wave & 3, wf = wave >> 2;
-  // With at least 8 evaluated partitions, every tile of a partition goes to
-  // the same XCD (workgroups are dealt to the 8 XCDs round-robin), so its L2
-  // serves the dZ1 rows to all feature tiles and the X rows to all hidden
-  // tiles; otherwise the tiles are spread over the chip.
+  // Work items are the partitions' row splits.  With at least 8 of them, every
+  // tile of an item goes to the same XCD (workgroups are dealt to the 8 XCDs
+  // round-robin), so its L2 serves the dZ1 rows to all feature tiles and the X
+  // rows to all hidden tiles; otherwise the tiles are spread over the chip.
   const int htiles = a.hidden / kWgBM, ftiles = (a.d_in + kWgBN - 1) / kWgBN;
-  const int tiles = htiles * ftiles;
-  int e, tile;
-  if (a.n_eval >= kXcds) {
-    const int local = static_cast<int>(blockIdx.x) / kXcds;
-    e = (local / tiles) * kXcds + static_cast<int>(blockIdx.x) % kXcds;
+  const int tiles = htiles * ftiles, items = a.n_eval * a.splits;
+  const int block = static_cast<int>(blockIdx.x);
+  int item, tile;
+  if (items >= kXcds) {
+    const int local = block / kXcds;
+    item = (local / tiles) * kXcds + block % kXcds;
     tile = local % tiles;
-    if (e >= a.n_eval) return;
+    if (item >= items) return;
   } else {
-    e = static_cast<int>(blockIdx.x) / tiles;
-    tile = static_cast<int>(blockIdx.x) % tiles;
+    item = block / tiles;
+    tile = block % tiles;
   }
+  const int e = item / a.splits, split = item % a.splits;
   const int64_t part = static_cast<int64_t>(e) * a.part_stride + a.part_offset;
   const int hb0 = (tile % htiles) * kWgBM;
   const int i0 = (tile / htiles) * kWgBN;
   const bool active = i0 + wf * (kWgBN / 2) < a.d_in;   // uniform per wave
   const bf16* Xp = a.X + part * a.m * a.d_in;
   const bf16* dz = a.dZ1 + mlp_dz1_index(a.m_pad, a.hidden, e, 0, 0);
-  const int ksteps = static_cast<int>(a.m_pad / kWgBK);
+  const int64_t steps = a.m_pad / kWgBK;   // at least one per split
+  const int k0 = static_cast<int>(split * steps / a.splits);
+  const int ksteps = static_cast<int>((split + 1) * steps / a.splits) - k0;
 
   // A chunk c = u * 512 + tid: row block c / 512, hidden (c % 512) / 2, slot
   // c % 2 holding half (c % 2) ^ swizzle; its source is that half of the row
@@ -609,13 +620,13 @@ void mlp_wgrad_kernel(MlpWgradArgs a) {
   auto stage_a = [&](int buf) { return reinterpret_cast<bf16*>(smem + buf * kWgStageBytes); };
   auto stage_b = [&](int buf) { return reinterpret_cast<bf16*>(smem + buf * kWgStageBytes + kWgAChunks * 16); };
   auto issue = [&](int ks, int buf) {
-    const bf16* dzk = dz + static_cast<int64_t>(ks) * (kWgBK / 16) * a.hidden * 16;
+    const bf16* dzk = dz + static_cast<int64_t>(k0 + ks) * (kWgBK / 16) * a.hidden * 16;
 #pragma unroll
     for (int u = 0; u < kWgALoads; ++u)
       load_lds16(dzk + aoff[u], stage_a(buf) + (u * kWgThreads + wave * 64) * 8);
 #pragma unroll
     for (int u = 0; u < kWgBLoads; ++u) {
-      const int64_t r = static_cast<int64_t>(ks) * kWgBK + brow[u];
+      const int64_t r = static_cast<int64_t>(k0 + ks) * kWgBK + brow[u];
       load_lds16(Xp + (r < a.m ? r : a.m - 1) * a.d_in + bcol[u], stage_b(buf) + (u * kWgThreads + wave * 64) * 8);
     }
   };
@@ -674,7 +685,8 @@ void mlp_wgrad_kernel(MlpWgradArgs a) {
   }
 
   if (!active) return;
-  float* slot = a.ring + (static_cast<int64_t>(a.plane) * a.n + part) * a.ld;
+  float* slot =
+      a.splits == 1 ? ring_slot(a, e) : a.split_sums + static_cast<int64_t>(item) * a.d_in * a.hidden;
 #pragma unroll
   for (int nt = 0; nt < 7; ++nt) {
     const int feat = i0 + wf * (kWgBN / 2) + nt * 16 + lr;
@@ -687,45 +699,77 @@ void mlp_wgrad_kernel(MlpWgradArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// reduce: rows partials -> ring (b1, W2 in [hidden][classes] order, b2)
+// reduce: the b1, W2 and b2 parts of the ring slots and, when the weight gradient
+// splits its rows, the splits' sums of dW1 (fp64, split order; 16 bytes per thread).
 // ---------------------------------------------------------------------------
 
-__global__ __launch_bounds__(256)
-void mlp_reduce_kernel(MlpReduceArgs a) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
-  if (j >= a.pstride) return;
+// Entry j of the rows kernel's sums over partition e (fp64, block order) -> the
+// b1, W2 ([hidden][classes] order) and b2 parts of the ring slot.
+__device__ __forceinline__ void reduce_small(const MlpSmallParts& r, const MlpWgradArgs& a, int64_t e, int64_t j) {
+  if (j >= r.pstride) return;
   const int64_t w1 = static_cast<int64_t>(a.d_in) * a.hidden;
   const int hw = kMlpMaxClasses * a.hidden;
   int64_t at;
   if (j < hw) {   // dW2^T in MFMA order: 16 units x 16 classes, four classes of one unit together
-    const int c = 4 * (j / 64 % 4) + j % 4, h = j / 256 * 16 + j / 4 % 16;
-    if (c >= a.classes) return;
-    at = w1 + a.hidden + static_cast<int64_t>(h) * a.classes + c;
+    const int i = static_cast<int>(j);
+    const int c = 4 * (i / 64 % 4) + i % 4, h = i / 256 * 16 + i / 4 % 16;
+    if (c >= r.classes) return;
+    at = w1 + a.hidden + static_cast<int64_t>(h) * r.classes + c;
   } else if (j < hw + a.hidden) {
     at = w1 + (j - hw);
   } else {
-    const int c = j - hw - a.hidden;
-    if (c >= a.classes) return;
-    at = w1 + a.hidden + static_cast<int64_t>(a.hidden) * a.classes + c;
+    const int c = static_cast<int>(j) - hw - a.hidden;
+    if (c >= r.classes) return;
+    at = w1 + a.hidden + static_cast<int64_t>(a.hidden) * r.classes + c;
   }
-  const int64_t e = blockIdx.y;
-  const int64_t part = e * a.part_stride + a.part_offset;
-  const int64_t tiles = a.tiles_per_part * a.n_eval;
-  const int64_t first = linear_row_block(tiles, a.blocks, e * a.tiles_per_part);
-  const int64_t last = linear_row_block(tiles, a.blocks, (e + 1) * a.tiles_per_part - 1);
-  const float* p = a.partials + (first + e) * a.pstride + j;
+  const int64_t tiles = r.tiles_per_part * a.n_eval;
+  const int64_t first = linear_row_block(tiles, r.blocks, e * r.tiles_per_part);
+  const int64_t last = linear_row_block(tiles, r.blocks, (e + 1) * r.tiles_per_part - 1);
+  const float* p = r.partials + (first + e) * r.pstride + j;
   const int count = static_cast<int>(last - first) + 1;
   double s = 0.0;
   int b = 0;
   for (; b + 8 <= count; b += 8) {
     float v[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) v[i] = p[static_cast<int64_t>(b + i) * a.pstride];
+    for (int i = 0; i < 8; ++i) v[i] = p[static_cast<int64_t>(b + i) * r.pstride];
 #pragma unroll
     for (int i = 0; i < 8; ++i) s += static_cast<double>(v[i]);
   }
-  for (; b < count; ++b) s += static_cast<double>(p[static_cast<int64_t>(b) * a.pstride]);
-  a.ring[(static_cast<int64_t>(a.plane) * a.n + part) * a.ld + at] = static_cast<float>(s);
+  for (; b < count; ++b) s += static_cast<double>(p[static_cast<int64_t>(b) * r.pstride]);
+  ring_slot(a, e)[at] = static_cast<float>(s);
+}
+
+__global__ __launch_bounds__(256)
+void mlp_reduce_kernel(MlpWgradArgs a, int fold_blocks) {
+  const int64_t e = blockIdx.y;
+  if (static_cast<int>(blockIdx.x) >= fold_blocks) {
+    reduce_small(a.small, a, e, (blockIdx.x - fold_blocks) * 256 + threadIdx.x);
+    return;
+  }
+  const int64_t q1 = static_cast<int64_t>(a.d_in) * a.hidden;
+  const int64_t i = (static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x) * 4;
+  if (i >= q1) return;
+  const float* p = a.split_sums + e * a.splits * q1 + i;
+  double sum[4] = {0.0, 0.0, 0.0, 0.0};
+  int b = 0;
+  for (; b + 4 <= a.splits; b += 4) {
+    f32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = *reinterpret_cast<const f32x4*>(p + (b + u) * q1);
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) sum[c] += static_cast<double>(v[u][c]);
+  }
+  for (; b < a.splits; ++b) {
+    const f32x4 v = *reinterpret_cast<const f32x4*>(p + b * q1);
+#pragma unroll
+    for (int c = 0; c < 4; ++c) sum[c] += static_cast<double>(v[c]);
+  }
+  const f32x4 out = {static_cast<float>(sum[0]), static_cast<float>(sum[1]), static_cast<float>(sum[2]),
+                     static_cast<float>(sum[3])};
+  *reinterpret_cast<f32x4*>(ring_slot(a, e) + i) = out;
 }
 
 // Row tiles of the rows kernel by hidden / 256 - 1: MT (16-row groups per tile)
@@ -739,6 +783,7 @@ const RowsShape kRows[4][kRowsShapes] = {
     {{6, mlp_rows_kernel<6, 6, 2>}, {4, mlp_rows_kernel<6, 4, 2>}, {2, mlp_rows_kernel<6, 2, 2>}},
     {{6, mlp_rows_kernel<8, 6, 2>}, {4, mlp_rows_kernel<8, 4, 2>}, {2, mlp_rows_kernel<8, 2, 2>}}};
 constexpr int kRowsBlocks = 256;   // one per CU
+constexpr int kMaxSplits = 32;
 
 }  // namespace
 
@@ -780,17 +825,42 @@ hipError_t launch_mlp_rows(const MlpRowsArgs& a, int32_t hidden, int shape, hipS
   return hipGetLastError();
 }
 
+// Row splits of the weight gradient.  A partition is hidden / 256 x d_in / 224
+// tiles, so few partitions leave most CUs idle: 4 x 5,000 rows at 784 x 512 are 32
+// blocks of 79 K steps, 124 us; in 7 splits 32 us and 6 us more in the reduce kernel.
+// Taken is the split that ends first by this estimate, in microseconds: rounds of
+// 256 blocks at 1.55 us per K step of 64 rows and 3 us to start and end, then the
+// splits' sums written and read at 4 TB/s.
+int mlp_wgrad_splits(int64_t m_pad, int32_t n_eval, int32_t d_in, int32_t hidden) {
+  const int64_t steps = m_pad / kWgBK;
+  const int64_t tiles = static_cast<int64_t>(hidden / kWgBM) * ((d_in + kWgBN - 1) / kWgBN) * n_eval;
+  const double bytes = 8.0 * n_eval * d_in * hidden;
+  int best = 1;
+  double best_cost = 0.0;
+  for (int s = 1; s <= std::min<int64_t>(steps, kMaxSplits); ++s) {
+    const double cost = static_cast<double>((tiles * s + 255) / 256) * (static_cast<double>((steps + s - 1) / s) * 1.55 + 3.0) +
+                        (s > 1 ? s * bytes / 4e6 + 4.0 : 0.0);
+    if (s == 1 || cost < best_cost) {
+      best = s;
+      best_cost = cost;
+    }
+  }
+  return best;
+}
+
 hipError_t launch_mlp_wgrad(const MlpWgradArgs& a, hipStream_t s) {
   const int tiles = (a.hidden / kWgBM) * ((a.d_in + kWgBN - 1) / kWgBN);
-  const int parts = a.n_eval >= kXcds ? (a.n_eval + kXcds - 1) / kXcds * kXcds : a.n_eval;
-  dim3 grid(static_cast<unsigned>(tiles * parts));
-  hipLaunchKernelGGL(mlp_wgrad_kernel, grid, dim3(kWgThreads), 0, s, a);
+  const int items = a.n_eval * a.splits;
+  const int parts = items >= kXcds ? (items + kXcds - 1) / kXcds * kXcds : items;
+  hipLaunchKernelGGL(mlp_wgrad_kernel, dim3(static_cast<unsigned>(tiles * parts)), dim3(kWgThreads), 0, s, a);
   return hipGetLastError();
 }
 
-hipError_t launch_mlp_reduce(const MlpReduceArgs& a, hipStream_t s) {
-  dim3 grid((a.pstride + 255) / 256, a.n_eval);
-  hipLaunchKernelGGL(mlp_reduce_kernel, grid, dim3(256), 0, s, a);
+hipError_t launch_mlp_reduce(const MlpWgradArgs& a, hipStream_t s) {
+  const int fold_blocks =
+      a.splits > 1 ? static_cast<int>((static_cast<int64_t>(a.d_in) * a.hidden / 4 + 255) / 256) : 0;
+  const int small_blocks = static_cast<int>((a.small.pstride + 255) / 256);
+  hipLaunchKernelGGL(mlp_reduce_kernel, dim3(fold_blocks + small_blocks, a.n_eval), dim3(256), 0, s, a, fold_blocks);
   return hipGetLastError();
 }
 
