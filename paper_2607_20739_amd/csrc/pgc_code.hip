@@ -72,10 +72,17 @@ void reduce_code_kernel(ReduceCodeArgs a) {
     const int e = pair / kFusedCols;
     const int64_t col = col0 + pair % kFusedCols;
     if (col >= ca.q) continue;
-    const int64_t rows = a.m * a.n_eval;
-    const int64_t first = linear_row_block(rows, a.blocks, e * a.m);
-    const int count = static_cast<int>(linear_row_block(rows, a.blocks, (e + 1) * a.m - 1) - first) + 1;
-    const float* p = a.partials + (first + (a.aligned ? 0 : e)) * ca.q + col;
+    int64_t first;
+    int count;
+    if (a.aligned) {   // equal numbers of sums
+      count = a.blocks / a.n_eval;
+      first = static_cast<int64_t>(e) * count;
+    } else {
+      const int64_t rows = a.m * a.n_eval, block = linear_row_block(rows, a.blocks, e * a.m);
+      count = static_cast<int>(linear_row_block(rows, a.blocks, (e + 1) * a.m - 1) - block) + 1;
+      first = block + e;
+    }
+    const float* p = a.partials + first * ca.q + col;
     // Loads go out 32 at a time (one memory latency per 32 partials); the
     // fp64 sum still runs in block order.
     double s = 0.0;
@@ -94,7 +101,14 @@ void reduce_code_kernel(ReduceCodeArgs a) {
 #pragma unroll
       for (int i = 0; i < 8; ++i) s += static_cast<double>(t[i]);
     }
-    for (; b < count; ++b) s += static_cast<double>(p[static_cast<int64_t>(b) * ca.q]);
+    if (b < count) {   // up to 7 more, one latency
+      float t[7];
+#pragma unroll
+      for (int i = 0; i < 7; ++i) t[i] = p[static_cast<int64_t>(min(b + i, count - 1)) * ca.q];
+#pragma unroll
+      for (int i = 0; i < 7; ++i)
+        if (b + i < count) s += static_cast<double>(t[i]);
+    }
     const float g = static_cast<float>(s * a.inv_m);
     const int64_t k = static_cast<int64_t>(e) * a.part_stride + a.part_offset;
     for (int pl = 0; pl < a.plane_count; ++pl)

@@ -9,13 +9,21 @@
 
 namespace pgc {
 
-// First of block b's rows when `blocks` blocks share `rows` rows (b = blocks: the end).
+// a / b for a >= 0, b > 0, in 32 bits where both fit: a 64-bit division takes a lane
+// some 0.5 us, which the smallest steps notice.
+__host__ __device__ inline int64_t short_div(int64_t a, int64_t b) {
+  return ((a | b) >> 32) == 0 ? static_cast<int64_t>(static_cast<uint32_t>(a) / static_cast<uint32_t>(b)) : a / b;
+}
+
+// First of block b's rows when `blocks` blocks share `rows` rows (b = blocks: the
+// end): floor(b * rows / blocks).
 __host__ __device__ inline int64_t linear_block_row(int64_t rows, int64_t blocks, int64_t b) {
-  return b * rows / blocks;
+  const int64_t each = short_div(rows, blocks);
+  return b * each + short_div(b * (rows - each * blocks), blocks);
 }
 // The block whose rows hold row r.
 __host__ __device__ inline int64_t linear_row_block(int64_t rows, int64_t blocks, int64_t r) {
-  return ((r + 1) * blocks - 1) / rows;
+  return short_div((r + 1) * blocks - 1, rows);
 }
 
 // Per-partition gradient of a linear model (Sec. III with a mean over each

@@ -12,6 +12,14 @@ __device__ __forceinline__ float dpp_move(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xF, 0xF, true));
 }
 
+// A value that is the same in every lane, in scalar registers (a division leaves its
+// result in vector ones).
+__device__ __forceinline__ int64_t uniform(int64_t v) {
+  const uint32_t lo = __builtin_amdgcn_readfirstlane(static_cast<int>(v));
+  const uint32_t hi = __builtin_amdgcn_readfirstlane(static_cast<int>(v >> 32));
+  return static_cast<int64_t>(static_cast<uint64_t>(hi) << 32 | lo);
+}
+
 // DPP controls of the 16-lane row reductions: swap neighbours, swap pairs,
 // mirror each half row, mirror the row.  After the two quad steps each lane
 // holds its quad's result; each mirror step combines a lane with one holding

@@ -122,9 +122,9 @@ void linear_gradient_kernel(LinearGradArgs a) {
   int buf = 0;
 
   // The block's run of the evaluated rows, counted through the partitions.
-  int64_t at = linear_block_row(a.rows, a.blocks, blockIdx.x);
-  const int64_t run_end = linear_block_row(a.rows, a.blocks, blockIdx.x + int64_t{1});
-  for (int64_t e = at / a.m; at < run_end; ++e) {
+  int64_t at = uniform(linear_block_row(a.rows, a.blocks, blockIdx.x));
+  const int64_t run_end = uniform(linear_block_row(a.rows, a.blocks, blockIdx.x + int64_t{1}));
+  for (int64_t e = uniform(short_div(at, a.m)); at < run_end; ++e) {
     const int64_t seg_end = min(run_end, (e + 1) * a.m);
     const int64_t skip = (e * a.part_stride + a.part_offset - e) * a.m;   // rows not evaluated before these
     const int64_t row_begin = at + skip, row_end = seg_end + skip;
@@ -188,13 +188,13 @@ void linear_gradient_kernel(LinearGradArgs a) {
     for (int v = 0; v < VEC; ++v) acc[v] = V{};
     // Whole iterations, from a place in the run of the block's own (see
     // linear_spread_starts) round to it again; then the remainder.
-    const int64_t whole = (row_end - row_begin) / kStep;
+    const int64_t whole = (row_end - row_begin) / kStep;   // a power of two
     const int64_t whole_end = row_begin + whole * kStep;
     int64_t start = row_begin;
     if (a.spread && whole > 1) {
       uint32_t h = blockIdx.x * 2654435761u;
       h = (h ^ (h >> 15)) * 0x85EBCA6Bu;
-      start += (h ^ (h >> 13)) % static_cast<uint32_t>(whole) * static_cast<int64_t>(kStep);
+      start += uniform((h ^ (h >> 13)) % static_cast<uint32_t>(whole)) * kStep;
     }
     int64_t base = start, end = whole_end;
     for (int lap = 0; lap < 2; ++lap, base = row_begin, end = start) {

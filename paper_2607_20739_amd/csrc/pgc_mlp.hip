@@ -232,8 +232,8 @@ void mlp_rows_kernel(MlpRowsArgs a) {
 
   const int64_t tiles_per_part = (a.m_pad + kBM - 1) / kBM;
   const int64_t tiles = tiles_per_part * a.n_eval;
-  int64_t t = linear_block_row(tiles, a.blocks, blockIdx.x);
-  const int64_t t_end = linear_block_row(tiles, a.blocks, blockIdx.x + int64_t{1});
+  int64_t t = uniform(linear_block_row(tiles, a.blocks, blockIdx.x));
+  const int64_t t_end = uniform(linear_block_row(tiles, a.blocks, blockIdx.x + int64_t{1}));
   const int kslices = a.kslices;
   const int dchunks = a.d_in / 8;
 
@@ -241,8 +241,8 @@ void mlp_rows_kernel(MlpRowsArgs a) {
   // lane % 8, which holds chunk slot ^ x_swizzle(row).
   const int xrow = wave * 2 * MT + (lane >> 3);
   auto tile_base = [&](int64_t tile, int64_t* r0) {
-    const int64_t e = tile / tiles_per_part;
-    *r0 = tile % tiles_per_part * kBM;
+    const int64_t e = uniform(short_div(tile, tiles_per_part));
+    *r0 = (tile - e * tiles_per_part) * kBM;
     return a.X + ((e * a.part_stride + a.part_offset) * a.m + min(*r0, a.m - 1)) * a.d_in;
   };
   // Rows past the partition read its last row, chunks past d_in the row's
@@ -284,7 +284,7 @@ void mlp_rows_kernel(MlpRowsArgs a) {
 
   int64_t run_e = -1;   // partition of the sums in this block's current slot
   for (; t < t_end; ++t) {
-    const int64_t e = t / tiles_per_part;
+    const int64_t e = uniform(short_div(t, tiles_per_part));
     const bool fresh = e != run_e;
     run_e = e;
 
@@ -497,7 +497,7 @@ void mlp_rows_kernel(MlpRowsArgs a) {
     }
     // Every wave has added its tiles' dZ2 (the barrier above): at the end of the
     // block's rows of a partition, their sum goes to the slot.
-    if (t + 1 == t_end || (t + 1) / tiles_per_part != e) {
+    if (t + 1 == t_end || t + 1 == (e + 1) * tiles_per_part) {
       if (wave == 0 && lane < 16) {
         float s = 0.0f;
 #pragma unroll
