@@ -736,7 +736,14 @@ __device__ __forceinline__ void reduce_small(const MlpSmallParts& r, const MlpWg
 #pragma unroll
     for (int i = 0; i < 8; ++i) s += static_cast<double>(v[i]);
   }
-  for (; b < count; ++b) s += static_cast<double>(p[static_cast<int64_t>(b) * r.pstride]);
+  if (b < count) {   // up to 7 more, one latency
+    float v[7];
+#pragma unroll
+    for (int i = 0; i < 7; ++i) v[i] = p[static_cast<int64_t>(min(b + i, count - 1)) * r.pstride];
+#pragma unroll
+    for (int i = 0; i < 7; ++i)
+      if (b + i < count) s += static_cast<double>(v[i]);
+  }
   ring_slot(a, e)[at] = static_cast<float>(s);
 }
 
@@ -776,12 +783,16 @@ void mlp_reduce_kernel(MlpWgradArgs a, int fold_blocks) {
 // and the ring's slices, largest tile first.
 using RowsKernel = void (*)(MlpRowsArgs);
 struct RowsShape { int mt; RowsKernel kernel; };
-constexpr int kRowsShapes = 3;
+constexpr int kRowsShapes = 4;
 const RowsShape kRows[4][kRowsShapes] = {
-    {{6, mlp_rows_kernel<2, 6, 4>}, {4, mlp_rows_kernel<2, 4, 4>}, {2, mlp_rows_kernel<2, 2, 4>}},
-    {{8, mlp_rows_kernel<4, 8, 3>}, {4, mlp_rows_kernel<4, 4, 3>}, {2, mlp_rows_kernel<4, 2, 3>}},
-    {{6, mlp_rows_kernel<6, 6, 2>}, {4, mlp_rows_kernel<6, 4, 2>}, {2, mlp_rows_kernel<6, 2, 2>}},
-    {{6, mlp_rows_kernel<8, 6, 2>}, {4, mlp_rows_kernel<8, 4, 2>}, {2, mlp_rows_kernel<8, 2, 2>}}};
+    {{6, mlp_rows_kernel<2, 6, 4>}, {4, mlp_rows_kernel<2, 4, 4>}, {2, mlp_rows_kernel<2, 2, 4>},
+     {1, mlp_rows_kernel<2, 1, 4>}},
+    {{8, mlp_rows_kernel<4, 8, 3>}, {6, mlp_rows_kernel<4, 6, 3>}, {4, mlp_rows_kernel<4, 4, 3>},
+     {2, mlp_rows_kernel<4, 2, 3>}},
+    {{6, mlp_rows_kernel<6, 6, 2>}, {5, mlp_rows_kernel<6, 5, 2>}, {4, mlp_rows_kernel<6, 4, 2>},
+     {2, mlp_rows_kernel<6, 2, 2>}},
+    {{6, mlp_rows_kernel<8, 6, 2>}, {5, mlp_rows_kernel<8, 5, 2>}, {4, mlp_rows_kernel<8, 4, 2>},
+     {2, mlp_rows_kernel<8, 2, 2>}}};
 constexpr int kRowsBlocks = 256;   // one per CU
 constexpr int kMaxSplits = 32;
 
@@ -789,7 +800,8 @@ constexpr int kMaxSplits = 32;
 
 // The tile that ends first by this estimate of a block's time, in clocks: per K
 // slice the MFMAs of its two waves per SIMD or the slice's W1F bytes from L2 at
-// 44 bytes per clock, whichever takes longer, then the softmax and dZ1.
+// 44 bytes per clock, whichever takes longer, then the softmax and dZ1.  4 x 5,000
+// rows at hidden 512: 212 tiles of 96 rows in 31 us, 160 of 128 in 36.
 MlpRowsGrid mlp_rows_grid(int64_t m_pad, int32_t n_eval, int32_t kslices, int32_t hidden) {
   const int nt = hidden / 128;
   MlpRowsGrid best;

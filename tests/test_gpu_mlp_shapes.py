@@ -23,11 +23,12 @@ BF16_TOL = 2e-2
 
 # n, m, d_in, hidden, classes
 SHAPES = [
-    (4, 100, 64, 256, 10), (4, 3000, 8, 256, 3), (3, 20000, 40, 256, 16),
-    (3, 700, 264, 512, 5), (4, 3400, 200, 512, 16), (3, 22000, 72, 512, 10),
-    (3, 65, 24, 768, 1 + 1), (4, 3400, 96, 768, 9), (3, 15990, 40, 768, 4),
-    (4, 1000, 32, 1024, 13), (4, 3400, 784, 1024, 10), (3, 16100, 104, 1024, 10),
-    (5, 1, 16, 1024, 2), (130 // 2, 33, 48, 256, 7),
+    (4, 100, 64, 256, 10), (4, 2000, 32, 256, 4), (4, 3000, 8, 256, 3), (3, 20000, 40, 256, 16),
+    (3, 700, 264, 512, 5), (4, 3400, 200, 512, 16), (3, 22000, 72, 512, 10), (4, 8100, 72, 512, 10),
+    (3, 65, 24, 768, 2), (4, 3400, 96, 768, 9), (4, 4400, 96, 768, 9), (3, 15990, 40, 768, 4),
+    (4, 1000, 32, 1024, 13), (4, 3400, 784, 1024, 10), (4, 5000, 72, 1024, 7),
+    (3, 16100, 104, 1024, 10),
+    (5, 1, 16, 1024, 2), (65, 33, 48, 256, 7),
 ]
 
 
