@@ -4,6 +4,8 @@
 // Sec. IV-A (FR encode / decode), Sec. V-A (real coefficients), Sec. V-B (CR).
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "pgc_kernels.h"
 
 namespace pgc {
@@ -63,9 +65,53 @@ void code_kernel(CodeArgs a) {
   }
 }
 
+// Loads N entries `stride` apart, from the `count`-th on the last one again.
+template <int N>
+__device__ __forceinline__ void load_up_to(float (&t)[N], const float* p, int count, int64_t stride) {
+#pragma unroll
+  for (int i = 0; i < N; ++i) t[i] = p[min(i, count - 1) * stride];
+}
+// Adds the first `count` of N entries to s, in order.
+template <int N>
+__device__ __forceinline__ void add_up_to(double& s, const float (&t)[N], int count) {
+#pragma unroll
+  for (int i = 0; i < N; ++i)
+    if (i < count) s += static_cast<double>(t[i]);
+}
+template <int N>
+__device__ __forceinline__ void load_and_add(double& s, const float* p, int count, int64_t stride) {
+  float t[N];
+  load_up_to(t, p, count, stride);
+  add_up_to(s, t, count);
+}
+
+template <int N>
+__device__ __forceinline__ void load_and_add_all(double& s, const float* p, int64_t stride) {
+  float t[N];
+#pragma unroll
+  for (int i = 0; i < N; ++i) t[i] = p[i * stride];
+  add_up_to(s, t, N);
+}
+
+// Sum in 64 bits and in order of `count` entries `stride` apart, with several loads in
+// flight and fewer than two per entry.
+__device__ __forceinline__ double strided_sum(const float* p, int count, int64_t stride) {
+  double s = 0.0;
+  int b = 0;
+  for (; b + 32 <= count; b += 32) load_and_add_all<32>(s, p + b * stride, stride);
+  for (; b + 8 <= count; b += 8) load_and_add_all<8>(s, p + b * stride, stride);
+  p += b * stride;
+  count -= b;
+  if (count > 4) load_and_add<7>(s, p, count, stride);
+  else if (count > 2) load_and_add<4>(s, p, count, stride);
+  else if (count > 0) load_and_add<2>(s, p, count, stride);
+  return s;
+}
+
 // Block b owns columns [16 b, 16 b + 16).  It first folds every evaluated
 // partition's block partials for those columns into the ring (fp64, block
-// order, one (partition, column) pair per thread), then -- after a barrier, so
+// order, one (partition, column) pair per thread and round; bound by a memory
+// latency and the index arithmetic of each round), then -- after a barrier, so
 // the fresh slots written by its own threads are visible -- encodes, decodes
 // and updates the same columns with the 16 lanes of each column splitting the
 // coded words.  No block depends on another.
@@ -77,51 +123,64 @@ void reduce_code_kernel(ReduceCodeArgs a) {
   __shared__ double part[kFusedSubs][kFusedCols];
   const CodeArgs& ca = a.code;
   const int64_t col0 = static_cast<int64_t>(blockIdx.x) * kFusedCols;
-  for (int pair = threadIdx.x; pair < a.n_eval * kFusedCols; pair += 256) {
-    const int e = pair / kFusedCols;
-    const int64_t col = col0 + pair % kFusedCols;
-    if (col >= ca.q) continue;
-    int64_t first;
-    int count;
-    if (a.aligned) {   // equal numbers of sums
-      count = a.blocks / a.n_eval;
-      first = static_cast<int64_t>(e) * count;
-    } else {
-      const int64_t rows = a.m * a.n_eval, block = linear_row_block(rows, a.blocks, e * a.m);
-      count = static_cast<int>(linear_row_block(rows, a.blocks, (e + 1) * a.m - 1) - block) + 1;
-      first = block + e;
-    }
-    const float* p = a.partials + first * ca.q + col;
-    // Loads go out 32 at a time (one memory latency per 32 partials); the
-    // fp64 sum still runs in block order.
-    double s = 0.0;
-    int b = 0;
-    for (; b + 32 <= count; b += 32) {
-      float t[32];
-#pragma unroll
-      for (int i = 0; i < 32; ++i) t[i] = p[static_cast<int64_t>(b + i) * ca.q];
-#pragma unroll
-      for (int i = 0; i < 32; ++i) s += static_cast<double>(t[i]);
-    }
-    for (; b + 8 <= count; b += 8) {
-      float t[8];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) t[i] = p[static_cast<int64_t>(b + i) * ca.q];
-#pragma unroll
-      for (int i = 0; i < 8; ++i) s += static_cast<double>(t[i]);
-    }
-    if (b < count) {   // up to 7 more, one latency
-      float t[7];
-#pragma unroll
-      for (int i = 0; i < 7; ++i) t[i] = p[static_cast<int64_t>(min(b + i, count - 1)) * ca.q];
-#pragma unroll
-      for (int i = 0; i < 7; ++i)
-        if (b + i < count) s += static_cast<double>(t[i]);
-    }
+  const float* const partials = a.partials;
+  const int pairs = a.n_eval * kFusedCols;
+  auto there = [&](int pair) { return pair < pairs && col0 + pair % kFusedCols < ca.q; };
+  auto put = [&](int pair, double s) {
     const float g = static_cast<float>(s * a.inv_m);
-    const int64_t k = static_cast<int64_t>(e) * a.part_stride + a.part_offset;
+    const int64_t k = static_cast<int64_t>(pair / kFusedCols) * a.part_stride + a.part_offset;
     for (int pl = 0; pl < a.plane_count; ++pl)
-      a.ring[((a.plane_first + pl) * static_cast<int64_t>(ca.n) + k) * ca.ld + col] = g;
+      a.ring[((a.plane_first + pl) * static_cast<int64_t>(ca.n) + k) * ca.ld + col0 + pair % kFusedCols] = g;
+  };
+  // Up to 4 partials per partition, as many workers with few rows leave them: a thread loads
+  // those of four pairs before it adds.  81 partitions of 16 rows of 371 features, one partial
+  // each, take 8.5 us (10.5 pair by pair with seven loads each); 84 of 1,304, four each, 10.4
+  // (11.9).
+  auto few = [&](auto most) {
+    constexpr int kMost = decltype(most)::value, kPairs = 4;
+    for (int pair = threadIdx.x; pair < pairs; pair += 256 * kPairs) {
+      float t[kPairs][kMost];
+#pragma unroll
+      for (int u = 0; u < kPairs; ++u) {
+        const int at = pair + 256 * u;
+        const int64_t first = static_cast<int64_t>(at / kFusedCols) * a.per_part;
+        if (there(at)) load_up_to(t[u], partials + first * ca.q + col0 + at % kFusedCols, a.per_part, ca.q);
+      }
+#pragma unroll
+      for (int u = 0; u < kPairs; ++u) {
+        if (!there(pair + 256 * u)) continue;
+        double s = 0.0;
+        add_up_to(s, t[u], a.per_part);
+        put(pair + 256 * u, s);
+      }
+    }
+  };
+  // range(e, &count): partition e's first partial.
+  auto many = [&](auto range) {
+    for (int pair = threadIdx.x; pair < pairs; pair += 256) {
+      if (!there(pair)) continue;
+      int count;
+      const int64_t first = range(pair / kFusedCols, &count);
+      put(pair, strided_sum(partials + first * ca.q + col0 + pair % kFusedCols, count, ca.q));
+    }
+  };
+  if (a.per_part == 1) {
+    few(std::integral_constant<int, 1>{});
+  } else if (a.per_part == 2) {
+    few(std::integral_constant<int, 2>{});
+  } else if (a.per_part == 3 || a.per_part == 4) {
+    few(std::integral_constant<int, 4>{});
+  } else if (a.per_part > 0) {   // equal numbers stay in scalar registers: 5.0 us for 5.4, 64 each of 12
+    many([&](int e, int* count) {
+      *count = a.per_part;
+      return static_cast<int64_t>(e) * a.per_part;
+    });
+  } else {
+    many([&](int e, int* count) {
+      const int64_t rows = a.m * a.n_eval, block = linear_row_block(rows, a.blocks, e * a.m);
+      *count = static_cast<int>(linear_row_block(rows, a.blocks, (e + 1) * a.m - 1) - block) + 1;
+      return block + e;
+    });
   }
   __syncthreads();
 

@@ -570,7 +570,7 @@ int linear_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc:
   ra.m = ctx->m;
   ra.n_eval = grid.n_eval;
   ra.blocks = grid.blocks;
-  ra.aligned = ga.aligned;
+  ra.per_part = grid.aligned ? grid.blocks / grid.n_eval : 0;
   ra.part_stride = part_stride;
   ra.part_offset = part_offset;
   ra.plane_first = plane_first;

@@ -105,7 +105,7 @@ struct ReduceCodeArgs {
   int64_t m;
   int32_t n_eval;
   int32_t blocks;
-  int32_t aligned;
+  int32_t per_part;        // partials of each e where the runs are aligned, else 0
   int32_t part_stride;
   int32_t part_offset;
   int32_t plane_first;

@@ -89,6 +89,33 @@ def test_blocks_that_cross_partitions(n, m, d):
         sess.close()
 
 
+# n, m: with 20,000 features a block takes at least a row, so min(256 / n, m) partials each.
+FOLDS = [(1, m) for m in (1, 2, 3, 4, 5, 7, 8, 9, 10, 12, 13, 31, 32, 33, 36, 39, 40, 71, 256)]
+FOLDS += [(3, 40), (17, 5), (40, 3), (64, 4), (60, 8), (64, 1), (85, 2), (128, 3), (130, 3), (256, 2)]
+
+
+@pytest.mark.parametrize("n,m", FOLDS)
+def test_folds_of_any_number_of_partials(n, m):
+    """Every remainder of the fold's batches of loads, and one to many rounds of its threads."""
+    d = 20000
+    _announce("fold n=%d m=%d d=%d" % (n, m, d))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(n * 1000 + m)
+    X = torch.randn(n * m, d, generator=g, device="cuda")
+    y = torch.randn(n * m, generator=g, device="cuda")
+    w = torch.zeros(d, device="cuda")
+    sess = P.PGCSession("CR", n, min(n, 2), "lsq", n * m, d)
+    try:
+        sess.step(X, y, w, np.zeros(n, np.uint8), 0.0)
+        for k in sorted({0, n // 3, n - 1}):
+            rows = slice(k * m, (k + 1) * m)
+            ref = _mean_gradient("lsq", X[rows], y[rows], w)
+            for slot in range(min(n, 2)):
+                assert normwise_error(sess.ring((k - slot) % n, slot).cpu().numpy(), ref) <= FP32_TOL, (k, slot)
+    finally:
+        sess.close()
+
+
 def test_any_base_address_gives_the_same_bits():
     n, m, d = 6, 211, 1000
     _announce("X and w at every float offset, d=%d" % d)
