@@ -279,6 +279,24 @@ def test_state_size_is_the_header_and_the_ring():
         P.pgc_destroy(ctx)
 
 
+@pytest.mark.parametrize("n,m,d", [(87, 17, 21020), (96, 30, 18944), (116, 24, 14316), (57, 30, 15132),
+                                   (26, 60, 23560), (60, 30, 26380)])
+def test_short_partitions_of_wide_rows_do_not_share_gradient_blocks(n, m, d):
+    """A block whose rows lie in two partitions leaves a partial sum for each; with few rows per
+    block the sums would be a large part of what a step moves.  The workspace holds the ring, the
+    coded words, the decoded gradient and the partials (4-byte values, 256-byte aligned parts): no
+    more than the whole blocks of 256 that fit the partitions."""
+    ctx = P.pgc_init("IS_SGD", n, 1, d)
+    try:
+        P.pgc_configure(ctx, "lsq", n * m, d)
+        ld = (d + 255) // 256 * 256
+        rest = P.pgc_workspace_bytes(ctx) - 4 * (2 * n * ld + d)
+        partials = rest // (4 * d)
+        assert n <= partials <= max(n, 256 // n * n), partials
+    finally:
+        P.pgc_destroy(ctx)
+
+
 def test_noalloc_step_rejects_on_the_host_before_any_device_work():
     """pgc_step_noalloc's argument checks run before it touches a GPU: an
     unconfigured context, the MLP, a shape whose block partial sums exceed the
