@@ -94,7 +94,9 @@ __device__ __forceinline__ void load_and_add_all(double& s, const float* p, int6
 }
 
 // Sum in 64 bits and in order of `count` entries `stride` apart, with several loads in
-// flight and fewer than two per entry.
+// flight.  kUniform: the count is the same for all lanes, and a remainder takes fewer than
+// two loads per entry; else the branches for that cost more than the loads.
+template <bool kUniform>
 __device__ __forceinline__ double strided_sum(const float* p, int count, int64_t stride) {
   double s = 0.0;
   int b = 0;
@@ -102,7 +104,7 @@ __device__ __forceinline__ double strided_sum(const float* p, int count, int64_t
   for (; b + 8 <= count; b += 8) load_and_add_all<8>(s, p + b * stride, stride);
   p += b * stride;
   count -= b;
-  if (count > 4) load_and_add<7>(s, p, count, stride);
+  if (count > 4 || (!kUniform && count > 0)) load_and_add<7>(s, p, count, stride);
   else if (count > 2) load_and_add<4>(s, p, count, stride);
   else if (count > 0) load_and_add<2>(s, p, count, stride);
   return s;
@@ -156,12 +158,12 @@ void reduce_code_kernel(ReduceCodeArgs a) {
     }
   };
   // range(e, &count): partition e's first partial.
-  auto many = [&](auto range) {
+  auto many = [&](auto uniform, auto range) {
     for (int pair = threadIdx.x; pair < pairs; pair += 256) {
       if (!there(pair)) continue;
       int count;
       const int64_t first = range(pair / kFusedCols, &count);
-      put(pair, strided_sum(partials + first * ca.q + col0 + pair % kFusedCols, count, ca.q));
+      put(pair, strided_sum<decltype(uniform)::value>(partials + first * ca.q + col0 + pair % kFusedCols, count, ca.q));
     }
   };
   if (a.per_part == 1) {
@@ -171,12 +173,12 @@ void reduce_code_kernel(ReduceCodeArgs a) {
   } else if (a.per_part == 3 || a.per_part == 4) {
     few(std::integral_constant<int, 4>{});
   } else if (a.per_part > 0) {   // equal numbers stay in scalar registers: 5.0 us for 5.4, 64 each of 12
-    many([&](int e, int* count) {
+    many(std::true_type{}, [&](int e, int* count) {
       *count = a.per_part;
       return static_cast<int64_t>(e) * a.per_part;
     });
   } else {
-    many([&](int e, int* count) {
+    many(std::false_type{}, [&](int e, int* count) {
       const int64_t rows = a.m * a.n_eval, block = linear_row_block(rows, a.blocks, e * a.m);
       *count = static_cast<int>(linear_row_block(rows, a.blocks, (e + 1) * a.m - 1) - block) + 1;
       return block + e;
