@@ -66,38 +66,38 @@ void code_kernel(CodeArgs a) {
 }
 
 // Loads N entries `stride` apart, from the `count`-th on the last one again.
-template <int N>
-__device__ __forceinline__ void load_up_to(float (&t)[N], const float* p, int count, int64_t stride) {
+template <class T, int N>
+__device__ __forceinline__ void load_up_to(T (&t)[N], const T* p, int count, int64_t stride) {
 #pragma unroll
   for (int i = 0; i < N; ++i) t[i] = p[min(i, count - 1) * stride];
 }
 // Adds the first `count` of N entries to s, in order.
-template <int N>
-__device__ __forceinline__ void add_up_to(double& s, const float (&t)[N], int count) {
+template <class T, int N>
+__device__ __forceinline__ void add_up_to(double& s, const T (&t)[N], int count) {
 #pragma unroll
   for (int i = 0; i < N; ++i)
     if (i < count) s += static_cast<double>(t[i]);
 }
-template <int N>
-__device__ __forceinline__ void load_and_add(double& s, const float* p, int count, int64_t stride) {
-  float t[N];
-  load_up_to(t, p, count, stride);
-  add_up_to(s, t, count);
+template <int N, class T>
+__device__ __forceinline__ void load_and_add(double& s, const T* p, int count, int64_t stride) {
+  T t[N];
+  load_up_to<T, N>(t, p, count, stride);
+  add_up_to<T, N>(s, t, count);
 }
 
-template <int N>
-__device__ __forceinline__ void load_and_add_all(double& s, const float* p, int64_t stride) {
-  float t[N];
+template <int N, class T>
+__device__ __forceinline__ void load_and_add_all(double& s, const T* p, int64_t stride) {
+  T t[N];
 #pragma unroll
   for (int i = 0; i < N; ++i) t[i] = p[i * stride];
-  add_up_to(s, t, N);
+  add_up_to<T, N>(s, t, N);
 }
 
 // Sum in 64 bits and in order of `count` entries `stride` apart, with several loads in
 // flight.  kUniform: the count is the same for all lanes, and a remainder takes fewer than
 // two loads per entry; else the branches for that cost more than the loads.
-template <bool kUniform>
-__device__ __forceinline__ double strided_sum(const float* p, int count, int64_t stride) {
+template <bool kUniform, class T>
+__device__ __forceinline__ double strided_sum(const T* p, int count, int64_t stride) {
   double s = 0.0;
   int b = 0;
   for (; b + 32 <= count; b += 32) load_and_add_all<32>(s, p + b * stride, stride);
@@ -110,29 +110,31 @@ __device__ __forceinline__ double strided_sum(const float* p, int count, int64_t
   return s;
 }
 
-// Block b owns columns [16 b, 16 b + 16).  It first folds every evaluated
+// Block b owns kCols columns from kCols b on.  It first folds every evaluated
 // partition's block partials for those columns into the ring (fp64, block
 // order, one (partition, column) pair per thread and round; bound by a memory
 // latency and the index arithmetic of each round), then -- after a barrier, so
 // the fresh slots written by its own threads are visible -- encodes, decodes
-// and updates the same columns with the 16 lanes of each column splitting the
-// coded words.  No block depends on another.
-constexpr int kFusedCols = 16;
-constexpr int kFusedSubs = 256 / kFusedCols;
+// and updates the same columns with the 256 / kCols lanes of each column splitting the
+// coded words.  No block depends on another.  fp64 partials take half as many columns, so
+// that a block reads no more bytes.
+constexpr int kFusedCols = 16, kWideCols = 8;
 
+template <class Partial, int kCols>
 __global__ __launch_bounds__(256)
 void reduce_code_kernel(ReduceCodeArgs a) {
-  __shared__ double part[kFusedSubs][kFusedCols];
+  constexpr int kSubs = 256 / kCols;
+  __shared__ double part[kSubs][kCols];
   const CodeArgs& ca = a.code;
-  const int64_t col0 = static_cast<int64_t>(blockIdx.x) * kFusedCols;
-  const float* const partials = a.partials;
-  const int pairs = a.n_eval * kFusedCols;
-  auto there = [&](int pair) { return pair < pairs && col0 + pair % kFusedCols < ca.q; };
+  const int64_t col0 = static_cast<int64_t>(blockIdx.x) * kCols;
+  const Partial* const partials = static_cast<const Partial*>(a.partials);
+  const int pairs = a.n_eval * kCols;
+  auto there = [&](int pair) { return pair < pairs && col0 + pair % kCols < ca.q; };
   auto put = [&](int pair, double s) {
     const float g = static_cast<float>(s * a.inv_m);
-    const int64_t k = static_cast<int64_t>(pair / kFusedCols) * a.part_stride + a.part_offset;
+    const int64_t k = static_cast<int64_t>(pair / kCols) * a.part_stride + a.part_offset;
     for (int pl = 0; pl < a.plane_count; ++pl)
-      a.ring[((a.plane_first + pl) * static_cast<int64_t>(ca.n) + k) * ca.ld + col0 + pair % kFusedCols] = g;
+      a.ring[((a.plane_first + pl) * static_cast<int64_t>(ca.n) + k) * ca.ld + col0 + pair % kCols] = g;
   };
   // Up to 4 partials per partition, as many workers with few rows leave them: a thread loads
   // those of four pairs before it adds.  81 partitions of 16 rows of 371 features, one partial
@@ -141,18 +143,18 @@ void reduce_code_kernel(ReduceCodeArgs a) {
   auto few = [&](auto most) {
     constexpr int kMost = decltype(most)::value, kPairs = 4;
     for (int pair = threadIdx.x; pair < pairs; pair += 256 * kPairs) {
-      float t[kPairs][kMost];
+      Partial t[kPairs][kMost];
 #pragma unroll
       for (int u = 0; u < kPairs; ++u) {
         const int at = pair + 256 * u;
-        const int64_t first = static_cast<int64_t>(at / kFusedCols) * a.per_part;
-        if (there(at)) load_up_to(t[u], partials + first * ca.q + col0 + at % kFusedCols, a.per_part, ca.q);
+        const int64_t first = static_cast<int64_t>(at / kCols) * a.per_part;
+        if (there(at)) load_up_to<Partial, kMost>(t[u], partials + first * ca.q + col0 + at % kCols, a.per_part, ca.q);
       }
 #pragma unroll
       for (int u = 0; u < kPairs; ++u) {
         if (!there(pair + 256 * u)) continue;
         double s = 0.0;
-        add_up_to(s, t[u], a.per_part);
+        add_up_to<Partial, kMost>(s, t[u], a.per_part);
         put(pair + 256 * u, s);
       }
     }
@@ -162,8 +164,8 @@ void reduce_code_kernel(ReduceCodeArgs a) {
     for (int pair = threadIdx.x; pair < pairs; pair += 256) {
       if (!there(pair)) continue;
       int count;
-      const int64_t first = range(pair / kFusedCols, &count);
-      put(pair, strided_sum<decltype(uniform)::value>(partials + first * ca.q + col0 + pair % kFusedCols, count, ca.q));
+      const int64_t first = range(pair / kCols, &count);
+      put(pair, strided_sum<decltype(uniform)::value>(partials + first * ca.q + col0 + pair % kCols, count, ca.q));
     }
   };
   if (a.per_part == 1) {
@@ -186,12 +188,12 @@ void reduce_code_kernel(ReduceCodeArgs a) {
   }
   __syncthreads();
 
-  const int lane = threadIdx.x % kFusedCols, sub = threadIdx.x / kFusedCols;
+  const int lane = threadIdx.x % kCols, sub = threadIdx.x / kCols;
   const int64_t col = col0 + lane;
   const bool live = col < ca.q;
   double ghat = 0.0;
   if (live) {
-    for (int j = sub; j < ca.n_coded; j += kFusedSubs) {
+    for (int j = sub; j < ca.n_coded; j += kSubs) {
       double word = 0.0;
       for (int o = 0; o < ca.c; ++o) {
         const int64_t slot = ca.fr ? static_cast<int64_t>(j) * ca.c + o
@@ -208,7 +210,7 @@ void reduce_code_kernel(ReduceCodeArgs a) {
   if (sub == 0 && live) {
     double g = part[0][lane];
 #pragma unroll
-    for (int i = 1; i < kFusedSubs; ++i) g += part[i][lane];
+    for (int i = 1; i < kSubs; ++i) g += part[i][lane];
     ca.decoded[col] = static_cast<float>(g);
     ca.w[col] = static_cast<float>(static_cast<double>(ca.w[col]) - ca.lr * g);
   }
@@ -217,9 +219,12 @@ void reduce_code_kernel(ReduceCodeArgs a) {
 }  // namespace
 
 hipError_t launch_reduce_code(const ReduceCodeArgs& a, hipStream_t stream) {
-  dim3 grid(static_cast<unsigned>((a.code.q + kFusedCols - 1) / kFusedCols));
-  hipLaunchKernelGGL(reduce_code_kernel, grid, dim3(256), 0, stream, a);
-  return hipGetLastError();
+  auto launch = [&](auto kernel, int cols) {
+    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((a.code.q + cols - 1) / cols)), dim3(256), 0, stream, a);
+    return hipGetLastError();
+  };
+  return a.wide ? launch(reduce_code_kernel<double, kWideCols>, kWideCols)
+                : launch(reduce_code_kernel<float, kFusedCols>, kFusedCols);
 }
 
 hipError_t launch_code(const CodeArgs& a, hipStream_t stream) {

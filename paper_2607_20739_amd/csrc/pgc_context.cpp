@@ -21,6 +21,11 @@ constexpr size_t kAlign = 256;
 // depend on the device.  Iterations and rows of a block from which its run may cross
 // a partition's end.
 constexpr int64_t kFlatIterations = 4, kFlatRows = 12;
+// Partials per partition up to which the narrow rows' are fp64: the fewer, the larger a part
+// of the gradient one is, and the more its rounding shows (16 features, 1,024 rows: error
+// 3.1e-8 against 64 bits, with fp32 partials 4.3e-8; folded in 32 bits from the start
+// 5.2e-8).  64 of them in fp64 would cost the fold 0.6 us and change nothing.
+constexpr int64_t kWidePartials = 16;
 // pgc_step_noalloc takes the shapes whose partial sums would fit its fixed array
 // on a grid of about this many blocks of equal whole row counts within each
 // partition, at least so many rows per block.
@@ -38,7 +43,9 @@ struct LinearGrid {
   int32_t n_eval = 0;
   int32_t blocks = 0;
   bool aligned = false;   // no run crosses a partition's end
+  bool wide = false;      // fp64 partials
   int64_t slots() const { return aligned ? blocks : blocks + int64_t{n_eval} - 1; }
+  int64_t partial_bytes() const { return slots() * (wide ? 8 : 4); }   // per feature
 };
 
 // Partial sums by which pgc_step_noalloc takes or refuses a shape.
@@ -74,6 +81,7 @@ LinearGrid make_linear_grid(int64_t m, int32_t n_eval, int64_t d) {
   }
   g.blocks = static_cast<int32_t>(blocks);
   g.aligned = blocks % n_eval == 0;
+  g.wide = shape.folds_wide && blocks / n_eval <= kWidePartials;
   return g;
 }
 
@@ -173,7 +181,7 @@ void compute_layout(pgc_ctx* ctx) {
     ctx->warm = make_linear_grid(ctx->m, n, q);
     ctx->pipe = make_linear_grid(ctx->m, n_pipe, q);
     ctx->off_partials =
-        take(sizeof(float) * static_cast<size_t>(std::max(ctx->warm.slots(), ctx->pipe.slots()) * q));
+        take(static_cast<size_t>(std::max(ctx->warm.partial_bytes(), ctx->pipe.partial_bytes()) * q));
     ctx->noalloc_bytes =
         sizeof(float) * static_cast<size_t>(std::max(noalloc_slots(ctx->m, n), noalloc_slots(ctx->m, n_pipe)) * q);
   }
@@ -559,6 +567,7 @@ int linear_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc:
   ga.d = static_cast<int32_t>(ctx->d);
   ga.blocks = grid.blocks;
   ga.aligned = grid.aligned ? 1 : 0;
+  ga.wide = grid.wide ? 1 : 0;
   ga.spread = pgc::linear_spread_starts(ga.rows, ga.blocks, ctx->d) ? 1 : 0;
   ga.part_stride = part_stride;
   ga.part_offset = part_offset;
@@ -573,6 +582,7 @@ int linear_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc:
   ra.n_eval = grid.n_eval;
   ra.blocks = grid.blocks;
   ra.per_part = grid.aligned ? grid.blocks / grid.n_eval : 0;
+  ra.wide = ga.wide;
   ra.part_stride = part_stride;
   ra.part_offset = part_offset;
   ra.plane_first = plane_first;

@@ -31,19 +31,21 @@ __host__ __device__ inline int64_t linear_row_block(int64_t rows, int64_t blocks
 // part_offset, e < n_eval, are counted through, and each of `blocks` blocks takes
 // an equal run of them.  For every partition that block b's run touches it sums
 //   slope(x_r . w, y_r) * x_r
-// over its rows there and writes the fp32 sum to partials[slot * d].  When the runs
+// over its rows there and writes the sum (fp64 when wide, else fp32) to
+// partials[slot * d].  When the runs
 // never cross a partition's end (aligned: n_eval divides blocks) slot = b, else
 // slot = b + e, which grows by one or two from each sum to the next.
 struct LinearGradArgs {
   const float* X;          // N x d row-major
   const float* y;          // N
   const float* w;          // d
-  float* partials;         // (blocks + (aligned ? 0 : n_eval - 1)) * d
+  void* partials;          // (blocks + (aligned ? 0 : n_eval - 1)) * d
   int64_t m;               // rows per partition
   int64_t rows;            // n_eval * m
   int32_t d;
   int32_t blocks;          // at most rows
   int32_t aligned;
+  int32_t wide;            // only where the shape folds in 64 bits
   int32_t spread;          // start each block at a scattered place in its run
   int32_t part_stride;
   int32_t part_offset;
@@ -53,12 +55,13 @@ struct LinearGradArgs {
 // Whether the step takes d features: up to PGC_MAX_LINEAR_D when d % 4 == 0 and X
 // and w are 16-byte aligned, else up to PGC_MAX_LINEAR_D_UNALIGNED.
 bool linear_grad_supported(int d, bool aligned16);
-// Blocks per launch that the gradient grid aims for, and the rows a block takes at
-// once (by d only, so the grid, and with it every result, is independent of pointer
+// Blocks per launch that the gradient grid aims for, the rows a block takes at
+// once, and whether it folds them in 64 bits (by d only, so the grid, and with it every result, is independent of pointer
 // alignment and device).
 struct LinearGradShape {
   int target_blocks;
   int rows_per_iteration;
+  bool folds_wide;
 };
 LinearGradShape linear_grad_shape(int d);
 
@@ -100,12 +103,13 @@ hipError_t launch_code(const CodeArgs& a, hipStream_t s);
 struct ReduceCodeArgs {
   CodeArgs code;
   float* ring;             // the ring code.ring reads, written here first
-  const float* partials;   // as LinearGradArgs::partials
+  const void* partials;    // as LinearGradArgs::partials
   double inv_m;
   int64_t m;
   int32_t n_eval;
   int32_t blocks;
   int32_t per_part;        // partials of each e where the runs are aligned, else 0
+  int32_t wide;            // fp64 partials
   int32_t part_stride;
   int32_t part_offset;
   int32_t plane_first;

@@ -19,7 +19,10 @@
 //     accumulator takes dump_rows rows, then moves to the lane's own sums in
 //     LDS, so that rounding does not grow with the rows of a block;
 //   * the rows sharing a wave and the GROUPS row groups of a block fold their
-//     sums in a fixed order, so one fp32 partial per block leaves the kernel;
+//     sums in a fixed order, so one partial per block leaves the kernel.  Rows of
+//     4 to 128 features, of which an iteration of a block takes 64 to 2,048, fold
+//     in 64 bits from the lane's sums on: in 32 bits the error of short runs is up
+//     to twice that of sums of 16 rows;
 //   * the evaluated rows of all partitions are cut into equal runs, one per
 //     block, whatever the number of partitions: a block whose run crosses into
 //     the next partition writes a partial for each.
@@ -82,6 +85,8 @@ __device__ __forceinline__ float loss_slope(float z, float y) {
 // the longest rows, whose runs hold few (d = 20,000 in 16 x 1,000 rows: error against
 // 64 bits 5.4e-8 instead of 5.7e-8, same time; d = 4,096 loses 0.5% to 8).
 constexpr int dump_rows(int waves) { return waves == 16 ? 8 : 16; }
+// Whether a row's sums fold in 64 bits (rows of 4 to 128 features).
+constexpr bool fold_wide(int vw, int lanes, int vec) { return vw == 4 && lanes < 64 && vec <= 2; }
 
 template <int MODEL, int VW, int LANES, int WAVES, int VEC, int GROUPS, int ROWS>
 __global__ __launch_bounds__(64 * WAVES * GROUPS)
@@ -114,13 +119,18 @@ void linear_gradient_kernel(LinearGradArgs a) {
     return x;
   };
 
-  V wv[VEC], acc[VEC];
+  // The accumulators of a chunk: an iteration's rows take turns, at most four each, and
+  // their sums join in 64 bits.
+  constexpr bool kWide = fold_wide(VW, LANES, VEC);
+  constexpr int kAccs = kWide && ROWS > 4 ? ROWS / 4 : 1;
+  V wv[VEC], acc[kAccs][VEC];
 #pragma unroll
   for (int v = 0; v < VEC; ++v) wv[v] = owned(v) ? plain_load<VW>(a.w + col(v)) : V{};
   wv[VEC - 1] = drop(wv[VEC - 1]);
 
   __shared__ float dots[2][GROUPS][ROWS][WAVES];
   __shared__ V sums[VEC][kGroupThreads * GROUPS];
+  __shared__ double wide[kWide ? GROUPS : 1][VEC][kWide ? 64 : 1];   // the row groups' folded sums
   int buf = 0;
 
   // The block's run of the evaluated rows, counted through the partitions.
@@ -130,13 +140,18 @@ void linear_gradient_kernel(LinearGradArgs a) {
     const int64_t seg_end = min(run_end, (e + 1) * a.m);
     const int64_t skip = (e * a.part_stride + a.part_offset - e) * a.m;   // rows not evaluated before these
     const int64_t row_begin = at + skip, row_end = seg_end + skip;
-    bool dumped = false;
+    bool dumped = false, held = false;   // sums in LDS, rows in the accumulators
     auto dump = [&] {
 #pragma unroll
       for (int v = 0; v < VEC; ++v) {
-        if (dumped) acc[v] += sums[v][threadIdx.x];
-        sums[v][threadIdx.x] = acc[v];
-        acc[v] = V{};
+#pragma unroll
+        for (int t = 1; t < kAccs; ++t) {
+          acc[0][v] += acc[t][v];
+          acc[t][v] = V{};
+        }
+        if (dumped) acc[0][v] += sums[v][threadIdx.x];
+        sums[v][threadIdx.x] = acc[0][v];
+        acc[0][v] = V{};
       }
       dumped = true;
     };
@@ -182,15 +197,17 @@ void linear_gradient_kernel(LinearGradArgs a) {
       for (int r = 0; r < ROWS; ++r) {
         const float slope = (!kRagged || r0 + r * kSubs < row_end) ? loss_slope<MODEL>(dot[r], label[r]) : 0.0f;
 #pragma unroll
-        for (int v = 0; v < VEC; ++v) acc[v] += slope * x[r][v];
+        for (int v = 0; v < VEC; ++v) acc[r % kAccs][v] += slope * x[r][v];
       }
     };
 
 #pragma unroll
-    for (int v = 0; v < VEC; ++v) acc[v] = V{};
+    for (int t = 0; t < kAccs; ++t)
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) acc[t][v] = V{};
     // Whole iterations, from a place in the run of the block's own (see
     // linear_spread_starts) round to it again; then the remainder.
-    const int64_t whole = (row_end - row_begin) / kStep;   // a power of two
+    const int64_t whole = (row_end - row_begin) / kStep;   // kStep is a power of two
     const int64_t whole_end = row_begin + whole * kStep;
     int64_t start = row_begin;
     if (a.spread && whole > 1) {
@@ -201,46 +218,79 @@ void linear_gradient_kernel(LinearGradArgs a) {
     int64_t base = start, end = whole_end;
     for (int lap = 0; lap < 2; ++lap, base = row_begin, end = start) {
       while (base < end) {
+        if (held) dump();
         for (int i = 0; i < dump_rows(WAVES) / ROWS && base < end; ++i, base += kStep) iterate(base, std::false_type{});
-        dump();
+        held = true;
       }
     }
-    if (whole_end < row_end) iterate(whole_end, std::true_type{});
-    if (dumped) {
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) acc[v] += sums[v][threadIdx.x];
+    if (whole_end < row_end) {
+      if (held) dump();
+      iterate(whole_end, std::true_type{});
     }
-
-    // Fold the wave's side-by-side rows, then the row groups.
+    // The lane's sums, then the wave's side-by-side rows and the row groups fold.
+    const int64_t slot = (blockIdx.x + (a.aligned ? 0 : e)) * static_cast<int64_t>(d);
+    if constexpr (kWide) {
+      // Lanes 16 i .. 16 i + 15 end with float i of the chunks.
+      typedef double W __attribute__((ext_vector_type(VW)));
+      const int i = lane / 16;
+      double total[VEC];
 #pragma unroll
-    for (int off = LANES; off < 64; off <<= 1)
+      for (int v = 0; v < VEC; ++v) {
+        W t = __builtin_convertvector(acc[0][v], W);
 #pragma unroll
-      for (int v = 0; v < VEC; ++v)
-#pragma unroll
-        for (int i = 0; i < VW; ++i) acc[v][i] += __shfl_xor(acc[v][i], off, 64);
-    if constexpr (GROUPS > 1) {
-      if (group > 0 && sub == 0) {
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) sums[v][threadIdx.x] = acc[v];
+        for (int u = 1; u < kAccs; ++u) t += __builtin_convertvector(acc[u][v], W);
+        if (dumped) t += __builtin_convertvector(sums[v][threadIdx.x], W);
+        total[v] = lane_stride_sums<LANES>(t);
+        if (group > 0) wide[group][v][lane] = total[v];
       }
       __syncthreads();
-      if (group == 0) {
+      if (group == 0 && lane % 16 < LANES) {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) {
+#pragma unroll
+          for (int g = 1; g < GROUPS; ++g) total[v] += wide[g][v][lane];
+          if (v < VEC - 1 || (own && keep >= VW - i)) {
+            const int64_t at = slot + col(v) + i;
+            if (a.wide) static_cast<double*>(a.partials)[at] = total[v];
+            else static_cast<float*>(a.partials)[at] = static_cast<float>(total[v]);
+          }
+        }
+      }
+    } else {
+      if (dumped) {
+#pragma unroll
+        for (int v = 0; v < VEC; ++v) acc[0][v] += sums[v][threadIdx.x];
+      }
+#pragma unroll
+      for (int off = LANES; off < 64; off <<= 1)
 #pragma unroll
         for (int v = 0; v < VEC; ++v)
 #pragma unroll
-          for (int g = 1; g < GROUPS; ++g) acc[v] += sums[v][g * kGroupThreads + threadIdx.x];
+          for (int i = 0; i < VW; ++i) acc[0][v][i] += __shfl_xor(acc[0][v][i], off, 64);
+      if constexpr (GROUPS > 1) {
+        if (group > 0 && sub == 0) {
+#pragma unroll
+          for (int v = 0; v < VEC; ++v) sums[v][threadIdx.x] = acc[0][v];
+        }
+        __syncthreads();
+        if (group == 0) {
+#pragma unroll
+          for (int v = 0; v < VEC; ++v)
+#pragma unroll
+            for (int g = 1; g < GROUPS; ++g) acc[0][v] += sums[v][g * kGroupThreads + threadIdx.x];
+        }
       }
-    }
-    if (group == 0 && sub == 0) {
-      float* out = a.partials + (blockIdx.x + (a.aligned ? 0 : e)) * static_cast<int64_t>(d);
+      if (group == 0 && sub == 0) {
+        float* out = static_cast<float*>(a.partials) + slot;
 #pragma unroll
-      for (int v = 0; v < VEC; ++v) {
-        if (v < VEC - 1 || (own && keep == VW)) {
-          plain_store<VW>(out + col(v), acc[v]);
-        } else if (own) {
+        for (int v = 0; v < VEC; ++v) {
+          if (v < VEC - 1 || (own && keep == VW)) {
+            plain_store<VW>(out + col(v), acc[0][v]);
+          } else if (own) {
 #pragma unroll
-          for (int i = 1; i < VW; ++i)
-            if (keep >= VW - i) out[last_col + i] = acc[v][i];
+            for (int i = 1; i < VW; ++i)
+              if (keep >= VW - i) out[last_col + i] = acc[0][v][i];
+          }
         }
       }
     }
@@ -333,7 +383,7 @@ bool linear_spread_starts(int64_t rows, int64_t blocks, int64_t d) {
 
 LinearGradShape linear_grad_shape(int d) {
   const Shape& s = shape_of(d);
-  return {s.blocks, s.groups * s.rows * (64 / s.lanes)};
+  return {s.blocks, s.groups * s.rows * (64 / s.lanes), fold_wide(d < 4 ? 1 : 4, s.lanes, s.vec)};
 }
 
 bool linear_grad_supported(int d, bool aligned16) {
