@@ -82,9 +82,13 @@ __device__ __forceinline__ float loss_slope(float z, float y) {
 }
 
 // Rows an accumulator sums before it moves to the lane's sums in LDS: 16, or 8 for
-// the longest rows, whose runs hold few (d = 20,000 in 16 x 1,000 rows: error against
-// 64 bits 5.4e-8 instead of 5.7e-8, same time; d = 4,096 loses 0.5% to 8).
+// the longest rows, whose runs hold few; d = 4,096 loses 0.5% to 8.
 constexpr int dump_rows(int waves) { return waves == 16 ? 8 : 16; }
+// Whether the accumulator starts again from what rounding took from the sum it moved to
+// (two-sum, Knuth), so that the moves add nothing to the error: for the longest rows, whose
+// blocks sum some 60 rows where sums of 16 would do for the fold in 64 bits (d = 20,000 in
+// 16 x 1,000 rows: error 6.3e-8, without 8.1e-8, of sums of 16 rows 7.6e-8; times within 1%).
+constexpr bool carry_rounding(int waves) { return waves == 16; }
 // Whether a row's sums fold in 64 bits (rows of 4 to 128 features).
 constexpr bool fold_wide(int vw, int lanes, int vec) { return vw == 4 && lanes < 64 && vec <= 2; }
 
@@ -122,6 +126,7 @@ void linear_gradient_kernel(LinearGradArgs a) {
   // The accumulators of a chunk: an iteration's rows take turns, at most four each, and
   // their sums join in 64 bits.
   constexpr bool kWide = fold_wide(VW, LANES, VEC);
+  constexpr bool kCarry = carry_rounding(WAVES);
   constexpr int kAccs = kWide && ROWS > 4 ? ROWS / 4 : 1;
   V wv[VEC], acc[kAccs][VEC];
 #pragma unroll
@@ -140,7 +145,9 @@ void linear_gradient_kernel(LinearGradArgs a) {
     const int64_t seg_end = min(run_end, (e + 1) * a.m);
     const int64_t skip = (e * a.part_stride + a.part_offset - e) * a.m;   // rows not evaluated before these
     const int64_t row_begin = at + skip, row_end = seg_end + skip;
-    bool dumped = false, held = false;   // sums in LDS, rows in the accumulators
+    // Sums in LDS, rows in the accumulators.  With kCarry every iteration's rows move at
+    // once (registers are few): LDS starts from zero and always holds the sums.
+    bool dumped = kCarry, held = false;
     auto dump = [&] {
 #pragma unroll
       for (int v = 0; v < VEC; ++v) {
@@ -149,9 +156,18 @@ void linear_gradient_kernel(LinearGradArgs a) {
           acc[0][v] += acc[t][v];
           acc[t][v] = V{};
         }
-        if (dumped) acc[0][v] += sums[v][threadIdx.x];
-        sums[v][threadIdx.x] = acc[0][v];
-        acc[0][v] = V{};
+        if constexpr (kCarry) {
+          const V old = sums[v][threadIdx.x], now = old + acc[0][v], part = now - old;
+          const V lost = (old - (now - part)) + (acc[0][v] - part);
+          sums[v][threadIdx.x] = now;
+#pragma unroll
+          for (int i = 0; i < VW; ++i) acc[0][v][i] = __builtin_isfinite(now[i]) ? lost[i] : 0.0f;
+          __builtin_amdgcn_sched_barrier(0);   // registers are few: one chunk after the other
+        } else {
+          if (dumped) acc[0][v] += sums[v][threadIdx.x];
+          sums[v][threadIdx.x] = acc[0][v];
+          acc[0][v] = V{};
+        }
       }
       dumped = true;
     };
@@ -205,6 +221,10 @@ void linear_gradient_kernel(LinearGradArgs a) {
     for (int t = 0; t < kAccs; ++t)
 #pragma unroll
       for (int v = 0; v < VEC; ++v) acc[t][v] = V{};
+    if constexpr (kCarry) {
+#pragma unroll
+      for (int v = 0; v < VEC; ++v) sums[v][threadIdx.x] = V{};
+    }
     // Whole iterations, from a place in the run of the block's own (see
     // linear_spread_starts) round to it again; then the remainder.
     const int64_t whole = (row_end - row_begin) / kStep;   // kStep is a power of two
@@ -218,13 +238,14 @@ void linear_gradient_kernel(LinearGradArgs a) {
     int64_t base = start, end = whole_end;
     for (int lap = 0; lap < 2; ++lap, base = row_begin, end = start) {
       while (base < end) {
-        if (held) dump();
+        if (!kCarry && held) dump();
         for (int i = 0; i < dump_rows(WAVES) / ROWS && base < end; ++i, base += kStep) iterate(base, std::false_type{});
-        held = true;
+        if constexpr (kCarry) dump();
+        else held = true;
       }
     }
     if (whole_end < row_end) {
-      if (held) dump();
+      if (!kCarry && held) dump();
       iterate(whole_end, std::true_type{});
     }
     // The lane's sums, then the wave's side-by-side rows and the row groups fold.
@@ -257,7 +278,7 @@ void linear_gradient_kernel(LinearGradArgs a) {
         }
       }
     } else {
-      if (dumped) {
+      if (kCarry || dumped) {
 #pragma unroll
         for (int v = 0; v < VEC; ++v) acc[0][v] += sums[v][threadIdx.x];
       }

@@ -149,6 +149,36 @@ def test_short_runs_of_narrow_rows_lose_no_more_than_sums_of_16_rows(n, m, d):
     assert mine <= chains
 
 
+def test_long_runs_of_the_longest_rows_lose_no_more_than_sums_of_16_rows():
+    """Blocks of the longest rows take some 60 of them.  As above, against chains of 16 rows."""
+    n, m, d = 16, 1000, 20000
+    _announce("precision n=%d m=%d d=%d" % (n, m, d))
+    mine, chains = [], []
+    for seed in range(3):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(seed)
+        X = torch.randn(n * m, d, generator=g, device="cuda")
+        y = torch.randint(2, (n * m,), generator=g, device="cuda").float()
+        sess = P.PGCSession("IS_SGD", n, 1, "logistic", n * m, d)
+        try:
+            sess.step(X, y, torch.zeros(d, device="cuda"), np.zeros(n, np.uint8), 0.1)
+            got = sess.ring(1, 0).double()
+        finally:
+            sess.close()
+        terms = (0.5 - y[m:2 * m])[:, None] * X[m:2 * m]
+        ref = terms.double().mean(dim=0)
+        terms = torch.nn.functional.pad(terms, (0, 0, 0, -m % 16)).view(-1, 16, d)
+        sums = terms[:, 0]
+        for i in range(1, 16):
+            sums = sums + terms[:, i]
+        sums = (sums.double().sum(dim=0) * (1.0 / m)).float().double()
+        mine.append(float((got - ref).norm() / ref.norm()))
+        chains.append(float((sums - ref).norm() / ref.norm()))
+    mine, chains = np.sqrt(np.mean(np.square(mine))), np.sqrt(np.mean(np.square(chains)))
+    print("  error %.3g, of sums of 16 rows %.3g" % (mine, chains), flush=True)
+    assert mine <= chains
+
+
 def test_any_base_address_gives_the_same_bits():
     n, m, d = 6, 211, 1000
     _announce("X and w at every float offset, d=%d" % d)
@@ -192,3 +222,24 @@ def test_infinite_features_reach_only_what_they_touch(d):
         fine = np.isfinite(ref)
         assert np.array_equal(np.isfinite(got), fine) and fine.sum() == d - 1, col
         assert normwise_error(got[fine], ref[fine]) <= FP32_TOL, col
+
+
+@pytest.mark.parametrize("d", [100, 4096, 16388, 32768])
+def test_an_infinite_sum_stays_infinite(d):
+    """Sums that overflow 32 bits early in a run of several moves to LDS: an infinite sum gives back
+    no rounding (that would be NaN), so its column ends infinite and the others as they were."""
+    n, m = 1, (1 << 26) // d
+    _announce("infinite sum, d=%d m=%d" % (d, m))
+    g = torch.Generator(device="cuda")
+    g.manual_seed(d)
+    X = torch.randn(n * m, d, generator=g, device="cuda")
+    y = torch.full((n * m,), 2.0, device="cuda")
+    w0 = torch.zeros(d, device="cuda")
+    X[0, 5] = X[m // 2, d - 2] = 0.0
+    plain, _ = _one_step("FR", "lsq", n, 1, X, y, w0)
+    X[0, 5], X[m // 2, d - 2] = 3e38, -3e38   # slope -2
+    got, _ = _one_step("FR", "lsq", n, 1, X, y, w0)
+    keep = torch.ones(d, dtype=torch.bool, device="cuda")
+    keep[5] = keep[d - 2] = False
+    assert got[5] == -float("inf") and got[d - 2] == float("inf")
+    assert torch.equal(got[keep], plain[keep])
