@@ -110,12 +110,25 @@ void linear_gradient_kernel(LinearGradArgs a) {
 
   // A lane's chunk v is columns col(v) .. col(v) + VW - 1.  Only the last one
   // can lie past the row (own false: never loaded) or cross its end (keep < VW:
-  // the lane's last `keep` floats are its own).
-  const int last = ((VEC - 1) * kRowLanes + row_lane) * VW;
-  const bool own = last < d;
-  const int keep = own ? min(d - last, VW) : VW;
+  // the lane's last `keep` floats are its own).  Two waves take a run of the row each,
+  // which they read from end to end: VEC - 1 chunks per lane and half of the rest, in whole
+  // cache lines.  Chunk by chunk in turn 4,096 features lose 0.5% at 4 GiB (592 us for 589)
+  // and 1.7% at 100 MiB; 3,584 and 4,040 gain 1% at 1 GiB.  More waves gain nothing from
+  // runs, and 16 lose up to 5%.
+  constexpr bool kRuns = WAVES == 2;
+  int first = row_lane * VW, end = d;
+  if constexpr (kRuns) {
+    const int rest = (d + VW - 1) / VW - 2 * (VEC - 1) * 64;   // 1 .. 128 chunks
+    const int split = ((VEC - 1) * 64 + min((rest + 15) / 16 * 8, rest - 1)) * VW;
+    first = lane * VW + (wave == 0 ? 0 : split);
+    if (wave == 0) end = split;
+  }
+  constexpr int kNext = (kRuns ? LANES : kRowLanes) * VW;   // columns to the lane's next chunk
+  const int last = first + (VEC - 1) * kNext;
+  const bool own = last < end;
+  const int keep = own ? min(d - last, VW) : VW;   // runs end with whole chunks but for the row's
   const int last_col = own ? last - (VW - keep) : 0;
-  auto col = [&](int v) { return v == VEC - 1 ? last_col : (v * kRowLanes + row_lane) * VW; };
+  auto col = [&](int v) { return v == VEC - 1 ? last_col : first + v * kNext; };
   auto owned = [&](int v) { return v < VEC - 1 || own; };
   auto drop = [&](V x) {
 #pragma unroll
