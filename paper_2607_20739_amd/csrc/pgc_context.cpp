@@ -166,7 +166,8 @@ void compute_layout(pgc_ctx* ctx) {
     const int32_t ks = static_cast<int32_t>(ctx->kslices);
     ctx->rows_warm = pgc::mlp_rows_grid(ctx->m_pad, n, ks, static_cast<int32_t>(hidden));
     ctx->rows_pipe = pgc::mlp_rows_grid(ctx->m_pad, n_pipe, ks, static_cast<int32_t>(hidden));
-    const int64_t slots = std::max(ctx->rows_warm.blocks + int64_t{n} - 1, ctx->rows_pipe.blocks + int64_t{n_pipe} - 1);
+    auto slots_of = [](const pgc::MlpRowsGrid& g, int32_t n_eval) { return int64_t{g.blocks} * g.runs + n_eval - 1; };
+    const int64_t slots = std::max(slots_of(ctx->rows_warm, n), slots_of(ctx->rows_pipe, n_pipe));
     ctx->off_w1f = take(2 * static_cast<size_t>(hidden * ctx->kslices * 32));
     ctx->off_w2t = take(2 * static_cast<size_t>(pgc::kMlpMaxClasses * hidden));
     ctx->off_w2p = take(2 * static_cast<size_t>(hidden * pgc::kMlpMaxClasses));
@@ -630,6 +631,7 @@ int mlp_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc::De
   ra.classes = classes;
   ra.n_eval = n_eval;
   ra.blocks = grid.blocks;
+  ra.runs = grid.runs;
   ra.part_stride = part_stride;
   ra.part_offset = part_offset;
   pgc::MlpWgradArgs wg{};
@@ -651,7 +653,7 @@ int mlp_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc::De
   wg.small.partials = partials;
   wg.small.tiles_per_part = grid.tiles_per_part;
   wg.small.pstride = ctx->pstride;
-  wg.small.blocks = grid.blocks;
+  wg.small.runs = grid.blocks * grid.runs;
   wg.small.classes = classes;
 
   int st = timed_launch(ctx, PGC_KERNEL_MLP_CAST, "MLP cast kernel",

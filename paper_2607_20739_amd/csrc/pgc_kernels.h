@@ -153,8 +153,9 @@ __host__ __device__ inline int64_t mlp_dz1_index(int64_t m_pad, int32_t hidden, 
 // H = bf16(relu(X W1 + b1)) of its rows, logits, softmax, dZ2 = (p - onehot(y)) / m,
 // and dZ1 = (dZ2 W2^T) masked by H > 0, written in the blocked layout above
 // (rows m .. m_pad - 1 as zeros).  The partitions' tiles_per_part row tiles are
-// counted through and `blocks` blocks take an equal run of them each; block b
-// writes the sums over its rows of partition e to partials[(b + e) * pstride]:
+// counted through and `blocks` blocks take an equal part of them each, in `runs` equal
+// runs; the sums over run r's rows (r < blocks * runs) of partition e go to
+// partials[(r + e) * pstride]:
 // dW2^T[16][hidden] in MFMA order (class 4 g + j of unit 16 ht + i at
 // ((ht * 4 + g) * 16 + i) * 4 + j; classes past the last group of four unwritten),
 // db1[hidden], db2[16].
@@ -170,11 +171,12 @@ struct MlpRowsArgs {
   float* partials;
   int64_t m, m_pad, pstride;
   float inv_m;
-  int32_t d_in, kslices, classes, n_eval, blocks, part_stride, part_offset;
+  int32_t d_in, kslices, classes, n_eval, blocks, runs, part_stride, part_offset;
 };
 struct MlpRowsGrid {
   int64_t tiles_per_part = 0;
   int32_t blocks = 0;
+  int32_t runs = 1;    // of a block
   int shape = 0;
 };
 MlpRowsGrid mlp_rows_grid(int64_t m_pad, int32_t n_eval, int32_t kslices, int32_t hidden);
@@ -184,7 +186,7 @@ hipError_t launch_mlp_rows(const MlpRowsArgs& a, int32_t hidden, int shape, hipS
 struct MlpSmallParts {
   const float* partials;
   int64_t tiles_per_part, pstride;
-  int32_t blocks, classes;
+  int32_t runs, classes;   // runs of all blocks
 };
 
 // dW1[i][h] = sum_r X[k*m + r][i] dZ1(e; r, h), written into the ring slot of

@@ -55,3 +55,41 @@ def test_partition_gradients_match_the_oracle(n, m, d, hidden, classes):
             assert max(errs) <= BF16_TOL
     finally:
         sess.close()
+
+
+@pytest.mark.parametrize("n,m,hidden", [(1, 1 << 20, 256), (1, 1 << 20, 1024), (2, (1 << 19) + 16 * 333, 768)])
+def test_sums_of_a_million_rows_lose_no_more_than_sums_of_1024(n, m, hidden):
+    """dW2 is a sum over rows whose terms are exact here: W1 copies features into the hidden layer,
+    W2 = 0 makes the softmax 1/2.  It may be off by no more than 32-bit sums of 1,024 rows, 16 at a
+    time, joined in 64 bits (random labels, so the sums wander; 64 columns of 4 draws)."""
+    d, classes = 64, 2
+    print("\n[gpu case] MLP precision n=%d m=%d hidden=%d" % (n, m, hidden), flush=True)
+    mine, chains = [], []
+    for seed in range(4):
+        g = torch.Generator(device="cuda")
+        g.manual_seed(seed)
+        X = torch.rand(n * m, d, generator=g, device="cuda").bfloat16()
+        y = torch.randint(2, (n * m,), generator=g, device="cuda", dtype=torch.int32)
+        W1 = torch.zeros(d, hidden, device="cuda")
+        W1[torch.arange(hidden) % d, torch.arange(hidden)] = 1.0
+        w = torch.cat([W1.reshape(-1), torch.zeros(hidden + hidden * classes + classes, device="cuda")])
+        sess = P.PGCSession("IS_SGD", n, 1, "mlp", n * m, d, hidden=hidden, classes=classes)
+        try:
+            sess.step(X, y, w, np.zeros(n, np.uint8), 0.0)
+            got = sess.ring(n - 1, 0)[d * hidden + hidden:-classes].view(hidden, classes)[:d, 0].double()
+        finally:
+            sess.close()
+        dz = (0.5 - (y[(n - 1) * m:] == 0).double()) * float(torch.tensor(1.0 / m))
+        terms = X[(n - 1) * m:].double() * dz.bfloat16().double()[:, None]
+        ref = terms.sum(dim=0)
+        steps = torch.nn.functional.pad(terms, (0, 0, 0, -m % 1024)).view(-1, 64, 16, d).sum(dim=2).float()
+        sums = steps[:, 0]
+        for i in range(1, 64):
+            sums = sums + steps[:, i]
+        sums = sums.double().sum(dim=0).float().double()
+        mine.append(float((got - ref).norm() / ref.norm()))
+        chains.append(float((sums - ref).norm() / ref.norm()))
+        del X, terms, steps
+    mine, chains = np.sqrt(np.mean(np.square(mine))), np.sqrt(np.mean(np.square(chains)))
+    print("  error %.3g, of sums of 1,024 rows %.3g" % (mine, chains), flush=True)
+    assert mine <= chains
