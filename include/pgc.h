@@ -181,8 +181,10 @@ int pgc_step(pgc_ctx* ctx, const void* X, const void* y, float* w,
  * The array used is the one of the current device, which must be the GPU of
  * the context's stream (as for any launch on that stream); its address is
  * looked up on the first call on each device.
- * Errors: PGC_EINVAL for the MLP, or when the configured shape's partial sums
- * exceed PGC_NOALLOC_SCRATCH_BYTES (at most 1024 gradient blocks of d floats);
+ * Errors: PGC_EINVAL for the MLP, or when the configured shape's partial sums (d
+ * floats each) on about 1024 gradient blocks, of at least 16 rows and within one
+ * partition each, would exceed PGC_NOALLOC_SCRATCH_BYTES (the blocks a step launches
+ * may be fewer or more; their sums fit the array for every shape that is taken);
  * PGC_EDEVICE if the array's device address cannot be found.  Every call on a
  * GPU uses that GPU's one array: calls that overlap on one GPU (contexts on
  * different streams) race and must be ordered by the caller.  The array keeps

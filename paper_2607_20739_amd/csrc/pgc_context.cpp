@@ -109,7 +109,7 @@ struct pgc_ctx {
   int64_t kslices = 0, m_pad = 0, pstride = 0;
   size_t off_ring = 0, off_coded = 0, off_decoded = 0, off_partials = 0, off_coef = 0, ws_need = 0;
   size_t off_w1f = 0, off_w2t = 0, off_w2p = 0, off_dz1 = 0, off_splits = 0;
-  size_t noalloc_bytes = 0;   // linear models: the partial sums pgc_step_noalloc accounts for
+  size_t partials_bytes = 0, noalloc_bytes = 0;   // linear models: linear_partials_bytes, noalloc_rule_bytes
   char* ws = nullptr;
   size_t ws_bytes = 0;
   hipStream_t stream = nullptr;
@@ -181,8 +181,8 @@ void compute_layout(pgc_ctx* ctx) {
   } else {
     ctx->warm = make_linear_grid(ctx->m, n, q);
     ctx->pipe = make_linear_grid(ctx->m, n_pipe, q);
-    ctx->off_partials =
-        take(static_cast<size_t>(std::max(ctx->warm.partial_bytes(), ctx->pipe.partial_bytes()) * q));
+    ctx->partials_bytes = static_cast<size_t>(std::max(ctx->warm.partial_bytes(), ctx->pipe.partial_bytes()) * q);
+    ctx->off_partials = take(ctx->partials_bytes);
     ctx->noalloc_bytes =
         sizeof(float) * static_cast<size_t>(std::max(noalloc_slots(ctx->m, n), noalloc_slots(ctx->m, n_pipe)) * q);
   }
@@ -686,7 +686,9 @@ int mlp_step(pgc_ctx* ctx, const void* X, const void* y, float* w, const pgc::De
 
 namespace pgc {
 
-size_t noalloc_partials_bytes(const pgc_ctx* ctx) { return ctx->noalloc_bytes; }
+size_t linear_partials_bytes(const pgc_ctx* ctx) { return ctx->partials_bytes; }
+
+size_t noalloc_rule_bytes(const pgc_ctx* ctx) { return ctx->noalloc_bytes; }
 
 bool context_is_linear(const pgc_ctx* ctx) { return ctx->configured && is_linear(ctx->cfg.model); }
 

@@ -47,11 +47,12 @@ extern "C" int pgc_step_noalloc(pgc_ctx* ctx, const void* X, const void* y, floa
   if (!pgc::context_is_configured(ctx)) return pgc::set_error(ctx, PGC_ESTATE, "pgc_configure first");
   if (!pgc::context_is_linear(ctx))
     return pgc::set_error(ctx, PGC_EINVAL, "pgc_step_noalloc runs the linear models only (PGC_LOGISTIC, PGC_LSQ)");
-  const size_t need = pgc::noalloc_partials_bytes(ctx);
-  if (need > PGC_NOALLOC_SCRATCH_BYTES) {
-    const std::string msg = "pgc_step_noalloc: the gradient's block partials need " + std::to_string(need) +
-                            " bytes, more than the fixed scratch of " +
-                            std::to_string(static_cast<size_t>(PGC_NOALLOC_SCRATCH_BYTES)) + " bytes";
+  const size_t rule = pgc::noalloc_rule_bytes(ctx), need = pgc::linear_partials_bytes(ctx);
+  if (rule > PGC_NOALLOC_SCRATCH_BYTES || need > PGC_NOALLOC_SCRATCH_BYTES) {
+    const std::string msg = "pgc_step_noalloc: the gradient's partials on about 1024 blocks would take " +
+                            std::to_string(rule) + " bytes (a step writes " + std::to_string(need) +
+                            "), more than the fixed scratch of " +
+                            std::to_string(static_cast<size_t>(PGC_NOALLOC_SCRATCH_BYTES)) + " bytes takes";
     return pgc::set_error(ctx, PGC_EINVAL, msg.c_str());
   }
   if (!pgc::context_has_workspace(ctx)) return pgc::set_error(ctx, PGC_ESTATE, "pgc_bind_workspace first");

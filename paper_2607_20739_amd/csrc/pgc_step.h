@@ -9,15 +9,19 @@
 
 namespace pgc {
 
-// pgc_step with the linear models' block partials at `partials` (device; at
-// least noalloc_partials_bytes(ctx) bytes), or in the bound workspace when
-// `partials` is null.  Same checks, errors and effects as pgc_step.
+// pgc_step with the linear models' block partials at `partials` (device, 8-byte
+// aligned; at least linear_partials_bytes(ctx) bytes), or in the bound workspace
+// when `partials` is null.  Same checks, errors and effects as pgc_step.
 int step_impl(pgc_ctx* ctx, const void* X, const void* y, float* w, const uint8_t* straggler_mask,
               float lr, float* partials);
 
-// Bytes of block partial sums by which pgc_step_noalloc accepts or refuses the
-// configured context: at least what a linear-model step of it writes.
-size_t noalloc_partials_bytes(const pgc_ctx* ctx);
+// The most bytes of block partials that a step of the configured context (a linear
+// model) writes.
+size_t linear_partials_bytes(const pgc_ctx* ctx);
+// The bytes by which pgc_step_noalloc takes (up to PGC_NOALLOC_SCRATCH_BYTES) or refuses
+// the configured context: those of the partials on a grid of about 1,024 blocks, not on
+// the grid that a step launches.  The grid of every shape that is taken fits.
+size_t noalloc_rule_bytes(const pgc_ctx* ctx);
 
 bool context_is_configured(const pgc_ctx* ctx);
 bool context_has_workspace(const pgc_ctx* ctx);

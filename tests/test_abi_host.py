@@ -5,6 +5,7 @@ and surviving sets bit for bit; the real-valued code's matrix and decode
 weights within 1e-12.  No device work is launched here.
 """
 
+import ctypes
 import itertools
 import os
 import re
@@ -332,6 +333,48 @@ def test_noalloc_step_rejects_on_the_host_before_any_device_work():
         assert P.pgc_get_step(ctx) == 0
     finally:
         P.pgc_destroy(ctx)
+
+
+def test_noalloc_rule_and_the_size_of_the_partials():
+    """pgc_step_noalloc takes the shapes whose sums on about 1,024 blocks of at least 16 rows, whole
+    blocks per partition, fit its array, and the array holds what the step of each of them writes.
+    linear_partials_bytes is that size: the workspace's last part, 256-byte aligned like the others."""
+    handle = P.lib()
+    # size_t pgc::linear_partials_bytes(const pgc_ctx*)
+    size_of = handle["_ZN3pgc21linear_partials_bytesEPK7pgc_ctx"]
+    size_of.restype, size_of.argtypes = ctypes.c_size_t, [ctypes.c_void_p]
+    draws = np.random.RandomState(3)
+    shapes = [("IS_SGD", 1, 1, 1100, 20000), ("IS_SGD", 16, 1, 16, 28488), ("CR", 4, 2, 2048, 32768)]
+    for _ in range(600):
+        scheme = draws.choice(["FR", "CR", "IS_SGD"])
+        c = 1 if scheme == "IS_SGD" else int(draws.randint(1, 5))
+        n = c * int(draws.randint(1, 257 // c)) if scheme == "FR" else int(draws.randint(c, 257))
+        shapes.append((scheme, n, c, int(np.exp(draws.uniform(0, 12))), int(np.exp(draws.uniform(0, np.log(32768))))))
+
+    def slots(m, parts):
+        b = min(-(-1024 // parts), -(-m // 16))
+        return parts * -(-m // -(-m // b))
+
+    taken = 0
+    for scheme, n, c, m, d in shapes:
+        ctx = P.pgc_init(scheme, n, c, d)
+        try:
+            P.pgc_configure(ctx, "lsq", n * m, d)
+            ld, fr = (d + 255) // 256 * 256, scheme == "FR"
+            parts = 4 * ((1 if fr else c) * n * ld), 4 * (n // c if fr else n) * ld, 4 * d
+            rest = P.pgc_workspace_bytes(ctx) - sum((b + 255) // 256 * 256 for b in parts)
+            size = size_of(ctx)
+            assert size > 0 and (size + 255) // 256 * 256 == rest, (scheme, n, c, m, d)
+            takes = 4 * d * max(slots(m, n), slots(m, n // c if fr else n)) <= P.PGC_NOALLOC_SCRATCH_BYTES
+            with pytest.raises(P.PGCError) as e:
+                P.pgc_step_noalloc(ctx, 1, 1, 1, np.zeros(n, np.uint8), 0.1, n)    # nothing is bound
+            assert e.value.status == (P.PGC_ESTATE if takes else P.PGC_EINVAL), (scheme, n, c, m, d)
+            assert not takes or size <= P.PGC_NOALLOC_SCRATCH_BYTES, (scheme, n, c, m, d)
+            assert takes or str(size) in P.pgc_last_error(ctx)
+            taken += takes
+        finally:
+            P.pgc_destroy(ctx)
+    assert 50 < taken < len(shapes) - 50
 
 
 def _random_admissible_case(data):
