@@ -28,13 +28,6 @@ constexpr int kDppSwap1 = 0xB1, kDppSwap2 = 0x4E, kDppHalfMirror = 0x141, kDppMi
 // Rotations of a row by 4 and 8 lanes.
 constexpr int kDppRor4 = 0x124, kDppRor8 = 0x128;
 
-__device__ __forceinline__ float row16_max(float v) {
-  v = fmaxf(v, dpp_move<kDppSwap1>(v));
-  v = fmaxf(v, dpp_move<kDppSwap2>(v));
-  v = fmaxf(v, dpp_move<kDppHalfMirror>(v));
-  return fmaxf(v, dpp_move<kDppMirror>(v));
-}
-
 __device__ __forceinline__ float row16_sum(float v) {
   v += dpp_move<kDppSwap1>(v);
   v += dpp_move<kDppSwap2>(v);

@@ -84,13 +84,8 @@ __device__ __forceinline__ void load_lds16(const void* src, void* lds_wave_base)
   __builtin_amdgcn_global_load_lds((global_void*)src, (lds_void*)lds_wave_base, 16, 0, 0);
 }
 
-// 16 bytes from a wave-uniform base plus a per-lane byte offset to LDS.
-__device__ __forceinline__ void load_lds16_at(const bf16* base, uint32_t offset_bytes, void* lds_wave_base) {
-  load_lds16(reinterpret_cast<const char*>(base) + offset_bytes, lds_wave_base);
-}
-
-// The same from a wave-uniform base plus a per-lane byte offset to a wave-uniform
-// LDS address, unknown to the compiler's wait insertion: before plain LDS reads
+// 16 bytes from a wave-uniform base plus a per-lane byte offset to a wave-uniform LDS
+// address, unknown to the compiler's wait insertion: before plain LDS reads
 // that follow the builtin it waits for every outstanding load of this kind (it
 // cannot tell the buffers apart), which would drain the prefetch.  The caller
 // orders the loads with wait_vmcnt and barriers; the compiler's own counted waits
