@@ -6,7 +6,8 @@ Every HIP and C++ source under csrc/ is compiled with
   --offload-arch=gfx950 -O3 -std=c++17 -fPIC
   -Xclang -target-feature -Xclang -packed-fp32-ops
 (the last pair keeps the compiler from emitting packed fp32 VALU instructions;
-the host pass reports the feature as unknown, which is harmless) and linked
+the host pass reports the feature as unknown, which is harmless and not shown;
+other warnings go to stderr) and linked
 into paper_2607_20739_amd/libpgc.so next to this file, linked against ROCm's
 roctx library for the per-step profiler ranges.
 """
@@ -41,12 +42,21 @@ def common_flags():
             "-I", INCLUDE, "-I", CSRC]
 
 
+def warnings(stderr):
+    """The compiler's warnings but for the host pass's about the feature it does not know."""
+    return [line for line in stderr.splitlines() if "warning" in line and "packed-fp32-ops" not in line
+            and not line.endswith("generated when compiling for host.")
+            and not line.endswith("generated when compiling for %s." % ARCH)]
+
+
 def _compile(src):
     obj = os.path.join(BUILD_DIR, os.path.basename(src) + ".o")
     cmd = [hipcc()] + common_flags() + ["-c", os.path.join(CSRC, src), "-o", obj]
     res = subprocess.run(cmd, capture_output=True, text=True)
     if res.returncode != 0:
         raise RuntimeError("compiling %s failed:\n%s\n%s" % (src, " ".join(cmd), res.stderr))
+    for line in warnings(res.stderr):
+        print(line, file=sys.stderr)
     return obj
 
 

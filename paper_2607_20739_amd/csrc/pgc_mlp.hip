@@ -89,10 +89,12 @@ __device__ __forceinline__ void load_lds16(const void* src, void* lds_wave_base)
 // that follow the builtin it waits for every outstanding load of this kind (it
 // cannot tell the buffers apart), which would drain the prefetch.  The caller
 // orders the loads with wait_vmcnt and barriers; the compiler's own counted waits
-// only get stricter by loads that it does not count.
+// only get stricter by loads that it does not count.  m0, which the load reads its LDS
+// address from when it is issued, is the compiler's to use: it is put back.
 __device__ __forceinline__ void load_lds16_async(const void* base, uint32_t offset_bytes, uint32_t lds_wave_base) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1"
-               :: "v"(offset_bytes), "s"(base), "s"(lds_wave_base) : "memory", "m0");
+  uint32_t m0;
+  asm volatile("s_mov_b32 %0, m0\n\ts_mov_b32 m0, %3\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, %2\n\ts_mov_b32 m0, %0"
+               : "=&s"(m0) : "v"(offset_bytes), "s"(base), "s"(lds_wave_base) : "memory");
 }
 
 // Workgroup barrier that orders LDS only: the wave's own LDS reads and writes
