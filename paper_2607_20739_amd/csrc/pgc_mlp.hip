@@ -549,15 +549,27 @@ static_assert(kWgStages * kWgStageBytes <= 160 * 1024, "LDS");
 __device__ __forceinline__ int wg_half_swizzle(int h) { return ((h >> 2) ^ (h >> 3)) & 1; }
 __device__ __forceinline__ int wg_row_swizzle(int r) { return 2 * ((r & 3) | (((r >> 3) & 1) << 2)); }
 
-// Transposing 8-byte LDS read, issued as inline assembly: for the builtin the
-// compiler waits for every outstanding direct-to-LDS load first (it cannot
-// tell the buffers apart), which would drain the prefetch.  The kernel's own
-// waits and barrier order the loads; the caller waits for lgkmcnt before use.
-__device__ __forceinline__ bf16x4v ds_read_tr16(const bf16* p) {
-  bf16x4v v;
-  const uint32_t addr = static_cast<uint32_t>(reinterpret_cast<uintptr_t>((lds_bf16x4*)p));
-  asm volatile("ds_read_b64_tr_b16 %0, %1" : "=v"(v) : "v"(addr));
-  return v;
+// The 2 x 7 transposing 8-byte LDS reads of a K half's X fragments: rows OFFSET and OFFSET +
+// 2,048 bytes past each address, and the wait for them.  Inline assembly, as for the builtin
+// the compiler waits for every outstanding direct-to-LDS load first (it cannot tell the
+// buffers apart), which would drain the prefetch; one block, as outside of it the compiler
+// takes the results as there from the start and may copy them.  The kernel's own waits and
+// barrier order the loads into LDS.
+template <int OFFSET>
+__device__ __forceinline__ void read_tr16_rows(const uint32_t (&at)[7], bf16x4v (&lo)[7], bf16x4v (&hi)[7]) {
+  asm volatile(
+      "ds_read_b64_tr_b16 %0, %14 offset:%21\n\tds_read_b64_tr_b16 %7, %14 offset:%22\n\t"
+      "ds_read_b64_tr_b16 %1, %15 offset:%21\n\tds_read_b64_tr_b16 %8, %15 offset:%22\n\t"
+      "ds_read_b64_tr_b16 %2, %16 offset:%21\n\tds_read_b64_tr_b16 %9, %16 offset:%22\n\t"
+      "ds_read_b64_tr_b16 %3, %17 offset:%21\n\tds_read_b64_tr_b16 %10, %17 offset:%22\n\t"
+      "ds_read_b64_tr_b16 %4, %18 offset:%21\n\tds_read_b64_tr_b16 %11, %18 offset:%22\n\t"
+      "ds_read_b64_tr_b16 %5, %19 offset:%21\n\tds_read_b64_tr_b16 %12, %19 offset:%22\n\t"
+      "ds_read_b64_tr_b16 %6, %20 offset:%21\n\tds_read_b64_tr_b16 %13, %20 offset:%22\n\t"
+      "s_waitcnt lgkmcnt(0)"
+      : "=&v"(lo[0]), "=&v"(lo[1]), "=&v"(lo[2]), "=&v"(lo[3]), "=&v"(lo[4]), "=&v"(lo[5]), "=&v"(lo[6]),
+        "=&v"(hi[0]), "=&v"(hi[1]), "=&v"(hi[2]), "=&v"(hi[3]), "=&v"(hi[4]), "=&v"(hi[5]), "=&v"(hi[6])
+      : "v"(at[0]), "v"(at[1]), "v"(at[2]), "v"(at[3]), "v"(at[4]), "v"(at[5]), "v"(at[6]), "n"(OFFSET),
+        "n"(OFFSET + 2048));
 }
 
 // The ring slot that evaluated partition e's gradient goes to.
@@ -640,23 +652,23 @@ void mlp_wgrad_kernel(MlpWgradArgs a) {
   for (int mt = 0; mt < 4; ++mt)
 #pragma unroll
     for (int nt = 0; nt < 7; ++nt) acc[mt][nt] = f32x4{};
+  // Feature 112 wf + 16 nt + 4 (lr & 3) .. + 3 of the tile sits in chunk 14 wf + 2 nt +
+  // ((lr & 3) >> 1), half (lr & 1), of rows 8 lg + (lr >> 2), + 4, + 32 and + 36, whose
+  // swizzle is the same.
+  const int brow0 = lg * 8 + (lr >> 2);
+  uint32_t bat[7];
+#pragma unroll
+  for (int nt = 0; nt < 7; ++nt)
+    bat[nt] = static_cast<uint32_t>(
+        (brow0 * kWgBRowSlots + ((14 * wf + 2 * nt + ((lr & 3) >> 1)) ^ wg_row_swizzle(brow0))) * 16 + (lr & 1) * 8);
   auto compute = [&](int buf) {
     const bf16* As = stage_a(buf);
-    const bf16* Bs = stage_b(buf);
+    const uint32_t Bs = lds_address(stage_b(buf));
+    uint32_t at[7];
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
-      const int row = kk * 32 + lg * 8 + (lr >> 2);
-      // Feature 112 wf + 16 nt + 4 (lr & 3) .. + 3 of the tile sits in chunk
-      // 14 wf + 2 nt + ((lr & 3) >> 1), half (lr & 1).
-      auto bpos = [&](int r, int nt) {
-        return (r * kWgBRowSlots + ((14 * wf + 2 * nt + ((lr & 3) >> 1)) ^ wg_row_swizzle(r))) * 8 + (lr & 1) * 4;
-      };
-      bf16x4v lo[7], hi[7];
-#pragma unroll
-      for (int nt = 0; nt < 7; ++nt) {
-        lo[nt] = ds_read_tr16(&Bs[bpos(row, nt)]);
-        hi[nt] = ds_read_tr16(&Bs[bpos(row + 4, nt)]);
-      }
+    for (int nt = 0; nt < 7; ++nt) at[nt] = Bs + bat[nt];
+    auto half = [&](auto kk_) {
+      constexpr int kk = decltype(kk_)::value;
       const int rb = kk * 2 + (lg >> 1), half = lg & 1;
       bf16x8 af[4];
 #pragma unroll
@@ -664,18 +676,17 @@ void mlp_wgrad_kernel(MlpWgradArgs a) {
         const int h = wh * 64 + mt * 16 + lr;
         af[mt] = *reinterpret_cast<const bf16x8*>(&As[((rb * kWgBM + h) * 2 + (half ^ wg_half_swizzle(h))) * 8]);
       }
-      // The transposing reads are invisible to the compiler's wait insertion:
-      // wait here, with every result tied to the wait so no use moves above it.
-      asm volatile("s_waitcnt lgkmcnt(0)"
-                   : "+v"(lo[0]), "+v"(lo[1]), "+v"(lo[2]), "+v"(lo[3]), "+v"(lo[4]), "+v"(lo[5]), "+v"(lo[6]),
-                     "+v"(hi[0]), "+v"(hi[1]), "+v"(hi[2]), "+v"(hi[3]), "+v"(hi[4]), "+v"(hi[5]), "+v"(hi[6]));
+      bf16x4v lo[7], hi[7];
+      read_tr16_rows<kk * 32 * kWgBRowSlots * 16>(at, lo, hi);
 #pragma unroll
       for (int nt = 0; nt < 7; ++nt) {
         const bf16x8 bv = {lo[nt][0], lo[nt][1], lo[nt][2], lo[nt][3], hi[nt][0], hi[nt][1], hi[nt][2], hi[nt][3]};
 #pragma unroll
         for (int mt = 0; mt < 4; ++mt) acc[mt][nt] = mfma_k32(af[mt], bv, acc[mt][nt]);
       }
-    }
+    };
+    half(std::integral_constant<int, 0>{});
+    half(std::integral_constant<int, 1>{});
   };
 
   issue(0, 0);

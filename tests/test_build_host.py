@@ -6,6 +6,7 @@ it may hold a value in all the same: such code has no defined behaviour.
 
 import concurrent.futures
 import os
+import re
 import subprocess
 
 import pytest
@@ -35,3 +36,17 @@ def test_warnings_are_found_in_the_compilers_output():
                       "1 warning generated when compiling for gfx950."])
     assert B.warnings(text) == ["a.hip:3:1: warning: unused function 'f' [-Wunused-function]"]
     assert B.warnings("") == []
+
+
+def test_inline_assembly_that_loads_registers_waits_for_them():
+    """The compiler takes the results of an assembly block as there when it ends: one that reads
+    memory into registers waits for it inside (loads that go to LDS have no results)."""
+    blocks = 0
+    for name in os.listdir(B.CSRC):
+        with open(os.path.join(B.CSRC, name)) as f:
+            text = f.read()
+        for block in re.findall(r"asm\s+volatile\s*\((.*?)\);", text, re.S):
+            if re.search(r"\b(ds_read|global_load_dword|buffer_load|s_load)", block):
+                blocks += 1
+                assert "s_waitcnt" in block, (name, block[:120])
+    assert blocks >= 2
