@@ -2,11 +2,14 @@
 
 Its shape follows the row length (lanes, waves and 16-byte chunks of a row), and
 its blocks take equal runs of the evaluated rows whatever the partitions, so the
-cases are row lengths on both sides of every class, with row counts that leave
-remainders everywhere, and few, many, long and very short partitions.  One step
-from w = 0 at lr = 1 gives w = -ghat, compared with the same mean gradient in
-float64 within the fp32 bar (1e-5 normwise).
+cases are row lengths on both sides of every class in partitions so short that most
+blocks have no whole iteration of rows, every class in runs of dozens of iterations
+that cross partitions, and few, many and very short partitions.  One step at lr = 1
+gives w = w0 - ghat, compared with the same mean gradient in float64 within the fp32
+bar (1e-5 normwise).
 """
+
+import ctypes
 
 import numpy as np
 import pytest
@@ -87,6 +90,49 @@ def test_blocks_that_cross_partitions(n, m, d):
             assert normwise_error(sess.ring(k, 0).cpu().numpy(), ref) <= FP32_TOL, k
     finally:
         sess.close()
+
+
+def _partials(n, m, d):
+    """Partial sums (32 bits) of a step that evaluates n partitions."""
+    size_of = P.lib()["_ZN3pgc21linear_partials_bytesEPK7pgc_ctx"]   # size_t (const pgc_ctx*)
+    size_of.restype, size_of.argtypes = ctypes.c_size_t, [ctypes.c_void_p]
+    ctx = P.pgc_init("IS_SGD", n, 1, d)
+    try:
+        P.pgc_configure(ctx, "lsq", n * m, d)
+        return size_of(ctx) / (4 * d)
+    finally:
+        P.pgc_destroy(ctx)
+
+
+@pytest.mark.parametrize("first", range(0, len(CLASSES) + 1, 5))
+def test_every_class_in_long_runs_that_cross_partitions(first):
+    """Runs from which blocks cross partition ends have at least four iterations and twelve rows;
+    here nine times as many, and some more rows: whole iterations from a scattered start round to
+    it, sums moved to LDS several times (every 16 rows of a lane at most), a remainder, and blocks
+    with rows of two partitions."""
+    for c in ([0] + CLASSES)[first:first + 5]:
+        n, d = 9, 3 if c == 0 else 4 * c if c == 1 or 4 * c > 8192 else 4 * c - 1
+        m = 16   # blocks within the partitions leave a multiple of n partials
+        while _partials(n, m, d) not in [blocks + n - 1 for blocks in (256, 512, 768, 1024)]:
+            m = m * 5 // 4 + 1
+            assert m < 1 << 20
+        m = 9 * m + 5
+        _announce("long runs d=%d n=%d m=%d, %d partials" % (d, n, m, _partials(n, m, d)))
+        assert (_partials(n, m, d) - n + 1) % 256 == 0
+        g = torch.Generator(device="cuda")
+        g.manual_seed(d)
+        X = torch.randn(n * m, d, generator=g, device="cuda")
+        y = torch.randn(n * m, generator=g, device="cuda")
+        w = torch.randn(d, generator=g, device="cuda") / d ** 0.5
+        sess = P.PGCSession("IS_SGD", n, 1, "lsq", n * m, d)
+        try:
+            sess.step(X, y, w, np.zeros(n, np.uint8), 0.0)
+            for k in (0, 3, n - 1):
+                rows = slice(k * m, (k + 1) * m)
+                ref = _mean_gradient("lsq", X[rows], y[rows], w)
+                assert normwise_error(sess.ring(k, 0).cpu().numpy(), ref) <= FP32_TOL, (d, k)
+        finally:
+            sess.close()
 
 
 # n, m: with 20,000 features a block takes at least a row, so min(256 / n, m) partials each.

@@ -1,12 +1,15 @@
 """The MLP gradient over the shapes at which its kernels change course: every row tile of the
 rows kernel at each hidden width (few, some and many rows), runs of tiles that cross
-partitions, tiles past a partition's rows, one and two K slices.
+partitions, tiles past a partition's rows, one and two K slices, and K loops long enough that
+every slot of the ring of W1 slices is used again.
 
 Each part of every partition's gradient (dW1, db1, dW2, db2) is compared with the fp64 oracle
 on the ring after the first step.  H, dZ2 and dZ1 are rounded to bf16 (2^-9 of each term at
 most), so a part is off by a few 2^-9 of its largest entry where few rows are summed: the bf16
 bar of 2e-2 covers that.
 """
+
+import ctypes
 
 import numpy as np
 import pytest
@@ -30,6 +33,43 @@ SHAPES = [
     (3, 16100, 104, 1024, 10),
     (5, 1, 16, 1024, 2), (65, 33, 48, 256, 7),
 ]
+
+
+class _Grid(ctypes.Structure):
+    _fields_ = [("tiles_per_part", ctypes.c_int64), ("blocks", ctypes.c_int32), ("runs", ctypes.c_int32),
+                ("shape", ctypes.c_int)]
+
+
+def _rows_grid(n, m, d, hidden):
+    """The rows kernel's grid: MlpRowsGrid pgc::mlp_rows_grid(m_pad, n_eval, kslices, hidden)."""
+    rule = P.lib()["_ZN3pgc13mlp_rows_gridEliii"]
+    rule.restype, rule.argtypes = _Grid, [ctypes.c_int64, ctypes.c_int32, ctypes.c_int32, ctypes.c_int32]
+    return rule((m + 63) // 64 * 64, n, (d + 31) // 32, hidden)
+
+
+def _rows_for(n, d, hidden, shape, rounds):
+    """The fewest rows per partition (of some) whose tile is the shape-th and whose blocks have at
+    least so many tiles."""
+    for m in list(range(43, 4000, 60)) + list(range(4003, 24000, 500)):
+        g = _rows_grid(n, m, d, hidden)
+        if g.shape == shape and g.tiles_per_part * n > (rounds - 1) * g.blocks:
+            return m
+    return None
+
+
+@pytest.mark.parametrize("d", [296, 328])   # 10 and 11 K slices; the ring has 4, 3 or 2 slots
+@pytest.mark.parametrize("shape", range(4))
+@pytest.mark.parametrize("hidden", [256, 512, 768, 1024])
+def test_every_row_tile_in_long_k_loops(hidden, shape, d):
+    """The ring's loads are ordered by counts of loads in flight, which apply from as many slices on
+    as the ring has and reuse a slot from one more; a wrong one reads a stale slice of W1."""
+    one, several = _rows_for(5, d, hidden, shape, 1), _rows_for(3, d, hidden, shape, 2)
+    assert one is not None and (several is not None or shape > 1)   # low tiles are for few rows
+    for n, m in ((5, one), (3, several)):
+        if m is None:
+            continue
+        assert _rows_grid(n, m, d, hidden).shape == shape
+        test_partition_gradients_match_the_oracle(n, m, d, hidden, 2 + (m + shape) % 15)
 
 
 @pytest.mark.parametrize("n,m,d,hidden,classes", SHAPES)
