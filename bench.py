@@ -302,8 +302,9 @@ def main():
         torch.cuda.synchronize()
         pass_ms.append(start.elapsed_time(stop))
     kernels = {"gradient": P.PGC_KERNEL_GRADIENT, "reduce": P.PGC_KERNEL_REDUCE, "code": P.PGC_KERNEL_CODE,
+               # mlp_forward: forward, softmax and the backward pass down to dZ1, one kernel.
                "mlp_cast": P.PGC_KERNEL_MLP_CAST, "mlp_forward": P.PGC_KERNEL_MLP_FORWARD,
-               "mlp_head": P.PGC_KERNEL_MLP_HEAD, "mlp_wgrad": P.PGC_KERNEL_MLP_WGRAD}
+               "mlp_wgrad": P.PGC_KERNEL_MLP_WGRAD}
     per_launch, timed_launches = {}, {}
     for kname, kid in kernels.items():
         ms, launches = P.pgc_kernel_time(sess.ctx, kid)

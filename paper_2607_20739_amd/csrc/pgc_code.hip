@@ -18,8 +18,9 @@ namespace {
 // the waves' decode partials are added in wave order.  Bound by HBM.  With more
 // bytes than the 256 MiB cache in front of it holds, ring and coded words are
 // streamed past the caches (kStream): 64 x 4 slots and 64 words of 814,090 columns,
-// 1.04 GB, take 180 us (5.8 TB/s) instead of 225; 20 MB take 10.0 us streamed,
-// 9.5 not, as part of the ring is still cached there.
+// 1.04 GB, take 180 us (5.8 TB/s) instead of 225; 497 MiB 91 instead of 109, 298 MiB 57
+// instead of 59 to 63.  20 MB take 10.0 us streamed, 9.5 not, as part of the ring is
+// still cached there.
 constexpr int kCodeCols = 256;
 constexpr int64_t kStreamBytes = int64_t{256} << 20;
 typedef float f4v __attribute__((ext_vector_type(4)));

@@ -819,8 +819,10 @@ constexpr int kMaxSplits = 32;
 
 // The tile that ends first by this estimate of a block's time, in clocks: per K
 // slice the MFMAs of its two waves per SIMD or the slice's W1F bytes from L2 at
-// 44 bytes per clock, whichever takes longer, then the softmax and dZ1.  4 x 5,000
-// rows at hidden 512: 212 tiles of 96 rows in 31 us, 160 of 128 in 36.
+// 44 bytes per clock, whichever takes longer, then the softmax and dZ1.  It serves
+// to compare tiles; with one tile per block, whose slices come from L2 for the first
+// time, a kernel takes about twice the estimate.  4 x 5,000 rows at hidden 512: 212
+// tiles of 96 rows in 29 us, 160 of 128 in 36.
 MlpRowsGrid mlp_rows_grid(int64_t m_pad, int32_t n_eval, int32_t kslices, int32_t hidden) {
   const int nt = hidden / 128;
   MlpRowsGrid best;
@@ -859,10 +861,12 @@ hipError_t launch_mlp_rows(const MlpRowsArgs& a, int32_t hidden, int shape, hipS
 
 // Row splits of the weight gradient.  A partition is hidden / 256 x d_in / 224
 // tiles, so few partitions leave most CUs idle: 4 x 5,000 rows at 784 x 512 are 32
-// blocks of 79 K steps, 124 us; in 7 splits 32 us and 6 us more in the reduce kernel.
-// Taken is the split that ends first by this estimate, in microseconds: rounds of
-// 256 blocks at 1.55 us per K step of 64 rows and 3 us to start and end, then the
-// splits' sums written and read at 4 TB/s.
+// blocks of 79 K steps, 120 us and 5 in the reduce kernel; in the 5 splits that the rule
+// picks 34 and 9 us.  Taken is the split that ends first by this estimate, in microseconds:
+// rounds of 256 blocks at 1.55 us per K step of 64 rows and 3 us to start and end, then
+// the splits' sums written and read at 4 TB/s.  It is not exact: sums that stay in the
+// 256 MiB cache cost a quarter of that, a K step of a short run 2.3 us, and 7 splits there
+// would take 29 and 10 us.
 int mlp_wgrad_splits(int64_t m_pad, int32_t n_eval, int32_t d_in, int32_t hidden) {
   const int64_t steps = m_pad / kWgBK;
   const int64_t tiles = static_cast<int64_t>(hidden / kWgBM) * ((d_in + kWgBN - 1) / kWgBN) * n_eval;

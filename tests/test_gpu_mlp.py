@@ -63,28 +63,28 @@ SMALL = [
     # d_in not a multiple of the K step (40 = 32 + 8), three classes, FR
     Workload("mlp_fr_small", "FR", "mlp", n=4, c=2, N=4 * 64, d=40, lr=0.05, steps=6,
              policy=POLICY_EXACT, cap=1, seed=32, hidden=256, classes=3),
-    # hidden = 512 (two forward column blocks, four head waves), c = n
+    # hidden = 512 (64 units per wave of the rows kernel, two tiles of the weight gradient), c = n
     Workload("mlp_cr_c_eq_n", "CR", "mlp", n=3, c=3, N=3 * 160, d=120, lr=0.02, steps=7,
              policy=POLICY_UNIFORM_COUNT, cap=2, seed=33, hidden=512, classes=16),
     # several tiles of every kernel: d_in = 456 spans three 224-wide feature tiles of the
-    # weight gradient (the last ragged), hidden = 768 three forward column tiles, m = 600
-    # two 384-row forward tiles (the last ragged, with a partial second epilogue pass)
+    # weight gradient (the last ragged), hidden = 768 three tiles of its other side, m = 600
+    # many row tiles, the last of a partition ragged
     Workload("mlp_cr_multi_tile", "CR", "mlp", n=4, c=2, N=4 * 600, d=456, lr=0.02, steps=5,
              policy=POLICY_EXACT, cap=1, seed=35, hidden=768, classes=7),
-    # five rows per partition: one ragged 16-row head tile, one 64-row weight-gradient K step,
-    # and a forward tile that is almost all clamped rows
+    # five rows per partition: one ragged 16-row group, one 64-row weight-gradient K step,
+    # and row tiles that are mostly clamped rows
     Workload("mlp_cr_tiny_partitions", "CR", "mlp", n=4, c=2, N=4 * 5, d=16, lr=0.05, steps=5,
              policy=POLICY_EXACT, cap=1, seed=36, hidden=256, classes=4),
-    # m = 385: a second 384-row forward tile holding one row; d_in = 72 pads to two 64-column
-    # K steps whose last one skips its upper half (columns 96 .. 127 lie past d_in), and ends
-    # in a half-filled 16-feature block of the weight gradient
+    # m = 385: a 16-row group of a row tile holding one row; d_in = 72 is two 64-column stages
+    # of X, the second a single 32-column slice that is mostly padding, and ends in a
+    # half-filled 16-feature block of the weight gradient
     Workload("mlp_cr_forward_tile_edge", "CR", "mlp", n=4, c=2, N=4 * 385, d=72, lr=0.05, steps=5,
              policy=POLICY_EXACT, cap=1, seed=38, hidden=256, classes=5),
     # the real-valued code on the MLP
     Workload("mlp_real_code", "CR_REAL", "mlp", n=4, c=2, N=4 * 64, d=64, lr=0.02, steps=5,
              policy=POLICY_EXACT, cap=1, seed=34, hidden=256, classes=10, code_seed=3),
-    # the smallest d_in (one 16-byte chunk per row: the forward's one K step is 56 columns of
-    # padding, the weight gradient's one feature tile 8 features wide) with the most classes
+    # the smallest d_in (one 16-byte chunk per row: the one K slice is 24 columns of padding,
+    # the weight gradient's one feature tile 8 features wide) with the most classes
     Workload("mlp_cr_min_din_max_classes", "CR", "mlp", n=4, c=2, N=4 * 64, d=8, lr=0.05, steps=5,
              policy=POLICY_EXACT, cap=1, seed=37, hidden=256, classes=16),
 ]
