@@ -111,31 +111,30 @@ __device__ __forceinline__ double strided_sum(const T* p, int count, int64_t str
   return s;
 }
 
-// Block b owns kCols columns from kCols b on.  It first folds every evaluated
+// Block b owns columns [16 b, 16 b + 16).  It first folds every evaluated
 // partition's block partials for those columns into the ring (fp64, block
 // order, one (partition, column) pair per thread and round; bound by a memory
 // latency and the index arithmetic of each round), then -- after a barrier, so
 // the fresh slots written by its own threads are visible -- encodes, decodes
-// and updates the same columns with the 256 / kCols lanes of each column splitting the
-// coded words.  No block depends on another.  fp64 partials take half as many columns, so
-// that a block reads no more bytes.
-constexpr int kFusedCols = 16, kWideCols = 8;
+// and updates the same columns with the 16 lanes of each column splitting the
+// coded words.  No block depends on another.
+constexpr int kFusedCols = 16;
+constexpr int kFusedSubs = 256 / kFusedCols;
 
-template <class Partial, int kCols>
+template <class Partial>
 __global__ __launch_bounds__(256)
 void reduce_code_kernel(ReduceCodeArgs a) {
-  constexpr int kSubs = 256 / kCols;
-  __shared__ double part[kSubs][kCols];
+  __shared__ double part[kFusedSubs][kFusedCols];
   const CodeArgs& ca = a.code;
-  const int64_t col0 = static_cast<int64_t>(blockIdx.x) * kCols;
+  const int64_t col0 = static_cast<int64_t>(blockIdx.x) * kFusedCols;
   const Partial* const partials = static_cast<const Partial*>(a.partials);
-  const int pairs = a.n_eval * kCols;
-  auto there = [&](int pair) { return pair < pairs && col0 + pair % kCols < ca.q; };
+  const int pairs = a.n_eval * kFusedCols;
+  auto there = [&](int pair) { return pair < pairs && col0 + pair % kFusedCols < ca.q; };
   auto put = [&](int pair, double s) {
     const float g = static_cast<float>(s * a.inv_m);
-    const int64_t k = static_cast<int64_t>(pair / kCols) * a.part_stride + a.part_offset;
+    const int64_t k = static_cast<int64_t>(pair / kFusedCols) * a.part_stride + a.part_offset;
     for (int pl = 0; pl < a.plane_count; ++pl)
-      a.ring[((a.plane_first + pl) * static_cast<int64_t>(ca.n) + k) * ca.ld + col0 + pair % kCols] = g;
+      a.ring[((a.plane_first + pl) * static_cast<int64_t>(ca.n) + k) * ca.ld + col0 + pair % kFusedCols] = g;
   };
   // Up to 4 partials per partition, as many workers with few rows leave them: a thread loads
   // those of four pairs before it adds.  81 partitions of 16 rows of 371 features, one partial
@@ -148,8 +147,8 @@ void reduce_code_kernel(ReduceCodeArgs a) {
 #pragma unroll
       for (int u = 0; u < kPairs; ++u) {
         const int at = pair + 256 * u;
-        const int64_t first = static_cast<int64_t>(at / kCols) * a.per_part;
-        if (there(at)) load_up_to<Partial, kMost>(t[u], partials + first * ca.q + col0 + at % kCols, a.per_part, ca.q);
+        const int64_t first = static_cast<int64_t>(at / kFusedCols) * a.per_part;
+        if (there(at)) load_up_to<Partial, kMost>(t[u], partials + first * ca.q + col0 + at % kFusedCols, a.per_part, ca.q);
       }
 #pragma unroll
       for (int u = 0; u < kPairs; ++u) {
@@ -165,8 +164,8 @@ void reduce_code_kernel(ReduceCodeArgs a) {
     for (int pair = threadIdx.x; pair < pairs; pair += 256) {
       if (!there(pair)) continue;
       int count;
-      const int64_t first = range(pair / kCols, &count);
-      put(pair, strided_sum<decltype(uniform)::value>(partials + first * ca.q + col0 + pair % kCols, count, ca.q));
+      const int64_t first = range(pair / kFusedCols, &count);
+      put(pair, strided_sum<decltype(uniform)::value>(partials + first * ca.q + col0 + pair % kFusedCols, count, ca.q));
     }
   };
   if (a.per_part == 1) {
@@ -189,12 +188,12 @@ void reduce_code_kernel(ReduceCodeArgs a) {
   }
   __syncthreads();
 
-  const int lane = threadIdx.x % kCols, sub = threadIdx.x / kCols;
+  const int lane = threadIdx.x % kFusedCols, sub = threadIdx.x / kFusedCols;
   const int64_t col = col0 + lane;
   const bool live = col < ca.q;
   double ghat = 0.0;
   if (live) {
-    for (int j = sub; j < ca.n_coded; j += kSubs) {
+    for (int j = sub; j < ca.n_coded; j += kFusedSubs) {
       double word = 0.0;
       for (int o = 0; o < ca.c; ++o) {
         const int64_t slot = ca.fr ? static_cast<int64_t>(j) * ca.c + o
@@ -211,7 +210,7 @@ void reduce_code_kernel(ReduceCodeArgs a) {
   if (sub == 0 && live) {
     double g = part[0][lane];
 #pragma unroll
-    for (int i = 1; i < kSubs; ++i) g += part[i][lane];
+    for (int i = 1; i < kFusedSubs; ++i) g += part[i][lane];
     ca.decoded[col] = static_cast<float>(g);
     ca.w[col] = static_cast<float>(static_cast<double>(ca.w[col]) - ca.lr * g);
   }
@@ -220,12 +219,10 @@ void reduce_code_kernel(ReduceCodeArgs a) {
 }  // namespace
 
 hipError_t launch_reduce_code(const ReduceCodeArgs& a, hipStream_t stream) {
-  auto launch = [&](auto kernel, int cols) {
-    hipLaunchKernelGGL(kernel, dim3(static_cast<unsigned>((a.code.q + cols - 1) / cols)), dim3(256), 0, stream, a);
-    return hipGetLastError();
-  };
-  return a.wide ? launch(reduce_code_kernel<double, kWideCols>, kWideCols)
-                : launch(reduce_code_kernel<float, kFusedCols>, kFusedCols);
+  dim3 grid(static_cast<unsigned>((a.code.q + kFusedCols - 1) / kFusedCols));
+  if (a.wide) hipLaunchKernelGGL(reduce_code_kernel<double>, grid, dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL(reduce_code_kernel<float>, grid, dim3(256), 0, stream, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_code(const CodeArgs& a, hipStream_t stream) {

@@ -282,7 +282,7 @@ void mlp_rows_kernel(MlpRowsArgs a) {
   // A tile's sums join those of its run (a block has one or a few) and partition.
   const int32_t runs = a.runs * a.blocks;
   int32_t run = blockIdx.x * a.runs;
-  int64_t run_end = uniform(linear_block_row(tiles, runs, run + 1));
+  int64_t run_end = a.runs == 1 ? t_end : uniform(linear_block_row(tiles, runs, run + 1));
   bool fresh = true;
   for (; t < t_end; ++t) {
     const int64_t e = uniform(short_div(t, tiles_per_part));
