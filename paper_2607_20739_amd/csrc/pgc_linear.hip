@@ -158,8 +158,10 @@ void linear_gradient_kernel(LinearGradArgs a) {
     const int64_t seg_end = min(run_end, (e + 1) * a.m);
     const int64_t skip = (e * a.part_stride + a.part_offset - e) * a.m;   // rows not evaluated before these
     const int64_t row_begin = at + skip, row_end = seg_end + skip;
-    // Sums in LDS, rows in the accumulators.  With kCarry every iteration's rows move at
-    // once (registers are few): LDS starts from zero and always holds the sums.
+    // Sums in LDS, rows in the accumulators.  With kCarry the rows move after their
+    // iterations, not before the next (registers are few): LDS starts from zero and always
+    // holds the sums, and what no rows follow stays (with 8 chunks it moves as well, for
+    // which the test would spill).
     bool dumped = kCarry, held = false;
     auto dump = [&] {
 #pragma unroll
@@ -253,8 +255,8 @@ void linear_gradient_kernel(LinearGradArgs a) {
       while (base < end) {
         if (!kCarry && held) dump();
         for (int i = 0; i < dump_rows(WAVES) / ROWS && base < end; ++i, base += kStep) iterate(base, std::false_type{});
-        if constexpr (kCarry) dump();
-        else held = true;
+        if constexpr (!kCarry) held = true;
+        else if (VEC == 8 || base < end || (lap == 0 && start > row_begin) || whole_end < row_end) dump();
       }
     }
     if (whole_end < row_end) {
