@@ -21,6 +21,8 @@ constexpr size_t kAlign = 256;
 // depend on the device.  Iterations and rows of a block from which its run may cross
 // a partition's end.
 constexpr int64_t kFlatIterations = 4, kFlatRows = 12;
+// Features of a row up to which three or four blocks of the launch share a CU.
+constexpr int64_t kSharedCuFeatures = 896;
 // Partials per partition up to which the narrow rows' are fp64: the fewer, the larger a part
 // of the gradient one is, and the more its rounding shows (16 features, 1,024 rows: error
 // 3.1e-8 against 64 bits, with fp32 partials 4.3e-8; folded in 32 bits from the start
@@ -61,8 +63,14 @@ int64_t noalloc_slots(int64_t m, int32_t n_eval) {
 // that crosses into the next partition costs a block a second fold, a second latency
 // and a second sum, which with few rows outweighs the CUs that stay idle (87 partitions
 // of 17 rows of 21,020 features: 342 sums of 256 blocks, 50 us a step; 174 of 174, 46.5;
-// 93 of 90 rows of 18,972: 127 against 134); and no block of less than an iteration,
-// whose sums would only make more to fold.
+// 93 of 90 rows of 18,972: 127 against 134).  Rows of more than kSharedCuFeatures features
+// then take no more blocks than give the longest run its number of iterations: one row
+// more than an iteration takes as long as two, and further blocks only leave more sums to
+// fold (29 partitions of 128 rows of 1,008 features, 4 to an iteration: 493 blocks 12.8 us
+// a step, 464 12.1; 85 of 4 rows of 30,000, one to an iteration: 255 blocks 36.7, 170
+// 31.8).  Narrower rows, of which three or four blocks share a CU, keep their blocks: a
+// sum is little beside a block's rows, and fewer blocks load the CUs unevenly (24 of 900
+// rows of 260: 768 blocks 13.0 us, 696 14.4; 24 of 800 of 700: 768 18.3, 600 19.0).
 LinearGrid make_linear_grid(int64_t m, int32_t n_eval, int64_t d) {
   const pgc::LinearGradShape shape = pgc::linear_grad_shape(static_cast<int>(d));
   LinearGrid g;
@@ -77,7 +85,9 @@ LinearGrid make_linear_grid(int64_t m, int32_t n_eval, int64_t d) {
   }
   if (!flat) {
     const int64_t iterations = (m + shape.rows_per_iteration - 1) / shape.rows_per_iteration;
-    blocks = n_eval * std::max<int64_t>(1, std::min(blocks / n_eval, iterations));
+    const int64_t most = std::max<int64_t>(1, std::min(blocks / n_eval, iterations));
+    const int64_t each = (iterations + most - 1) / most;
+    blocks = n_eval * (d > kSharedCuFeatures ? (iterations + each - 1) / each : most);
   }
   g.blocks = static_cast<int32_t>(blocks);
   g.aligned = blocks % n_eval == 0;

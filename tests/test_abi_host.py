@@ -298,6 +298,26 @@ def test_short_partitions_of_wide_rows_do_not_share_gradient_blocks(n, m, d):
         P.pgc_destroy(ctx)
 
 
+@pytest.mark.parametrize("n,m,d,step", [(29, 128, 1008, 4), (5, 413, 1228, 4), (20, 110, 1500, 4), (3, 700, 2040, 4),
+                                        (85, 4, 30000, 1), (64, 5, 20000, 1), (40, 50, 5000, 4), (60, 64, 900, 4)])
+def test_blocks_of_wide_rows_are_no_more_than_their_iterations_need(n, m, d, step):
+    """A block reads `step` rows at a time, and part of them takes as long as all: with one block
+    less per partition the longest run would take an iteration more."""
+    handle = P.lib()
+    size_of = handle["_ZN3pgc21linear_partials_bytesEPK7pgc_ctx"]   # size_t (const pgc_ctx*)
+    size_of.restype, size_of.argtypes = ctypes.c_size_t, [ctypes.c_void_p]
+    ctx = P.pgc_init("IS_SGD", n, 1, d)
+    try:
+        P.pgc_configure(ctx, "lsq", n * m, d)
+        partials = size_of(ctx) // (4 * d)
+    finally:
+        P.pgc_destroy(ctx)
+    assert partials % n == 0
+    blocks = partials // n
+    iterations = lambda b: -(-(-(-m // b)) // step)
+    assert blocks == 1 or iterations(blocks - 1) > iterations(blocks), blocks
+
+
 def test_noalloc_step_rejects_on_the_host_before_any_device_work():
     """pgc_step_noalloc's argument checks run before it touches a GPU: an
     unconfigured context, the MLP, a shape whose block partial sums exceed the
