@@ -19,8 +19,8 @@ namespace {
 constexpr size_t kAlign = 256;
 // The linear gradient's grid depends only on the problem shape, so results do not
 // depend on the device.  Iterations and rows of a block from which its run may cross
-// a partition's end.
-constexpr int64_t kFlatIterations = 4, kFlatRows = 12;
+// a partition's end, and the rows from which it does whatever the partitions.
+constexpr int64_t kFlatIterations = 4, kFlatRows = 12, kLongRows = 24;
 // Features of a row up to which three or four blocks of the launch share a CU.
 constexpr int64_t kSharedCuFeatures = 896;
 // Partials per partition up to which the narrow rows' are fp64: the fewer, the larger a part
@@ -63,7 +63,11 @@ int64_t noalloc_slots(int64_t m, int32_t n_eval) {
 // that crosses into the next partition costs a block a second fold, a second latency
 // and a second sum, which with few rows outweighs the CUs that stay idle (87 partitions
 // of 17 rows of 21,020 features: 342 sums of 256 blocks, 50 us a step; 174 of 174, 46.5;
-// 93 of 90 rows of 18,972: 127 against 134).  Rows of more than kSharedCuFeatures features
+// 93 of 90 rows of 18,972: 127 against 134).  Up to kLongRows rows per block the same
+// holds where the partitions divide well, that is where their blocks take no more than
+// the one iteration that a crossing costs beyond equal runs (117 of 30 rows of 20,308: 15
+// iterations for 14, 78 us for 86; 66 of 150 of 1,004: 6 for 5, 19.1 for 23.1; but 86 of
+// 60 of 9,000: 15 for 11, 53.1 for 50.4).  Rows of more than kSharedCuFeatures features
 // then take no more blocks than give the longest run its number of iterations: one row
 // more than an iteration takes as long as two, and further blocks only leave more sums to
 // fold (29 partitions of 128 rows of 1,008 features, 4 to an iteration: 493 blocks 12.8 us
@@ -76,7 +80,16 @@ LinearGrid make_linear_grid(int64_t m, int32_t n_eval, int64_t d) {
   LinearGrid g;
   g.n_eval = n_eval;
   int64_t blocks = shape.target_blocks;
-  bool flat = m * n_eval >= blocks * std::max(kFlatIterations * shape.rows_per_iteration, kFlatRows);
+  const int64_t step = shape.rows_per_iteration;
+  const int64_t iterations = (m + step - 1) / step;
+  // A block's, with equal blocks within each partition.
+  auto iterations_within = [&] {
+    const int64_t most = std::max<int64_t>(1, std::min(blocks / n_eval, iterations));
+    return (iterations + most - 1) / most;
+  };
+  bool flat = m * n_eval >= blocks * std::max(kFlatIterations * step, kFlatRows);
+  if (flat && m * n_eval < blocks * kLongRows)
+    flat = iterations_within() > (m * n_eval + blocks * step - 1) / (blocks * step) + 1;
   // pgc_step_noalloc's array holds the sums of every shape it takes.
   const int64_t fit = PGC_NOALLOC_SCRATCH_BYTES / (sizeof(float) * d);
   if (flat && blocks + n_eval - 1 > fit && noalloc_slots(m, n_eval) <= fit) {
@@ -84,10 +97,9 @@ LinearGrid make_linear_grid(int64_t m, int32_t n_eval, int64_t d) {
     flat = false;
   }
   if (!flat) {
-    const int64_t iterations = (m + shape.rows_per_iteration - 1) / shape.rows_per_iteration;
-    const int64_t most = std::max<int64_t>(1, std::min(blocks / n_eval, iterations));
-    const int64_t each = (iterations + most - 1) / most;
-    blocks = n_eval * (d > kSharedCuFeatures ? (iterations + each - 1) / each : most);
+    const int64_t each = iterations_within();
+    blocks = n_eval * (d > kSharedCuFeatures ? (iterations + each - 1) / each
+                                             : std::max<int64_t>(1, std::min(blocks / n_eval, iterations)));
   }
   g.blocks = static_cast<int32_t>(blocks);
   g.aligned = blocks % n_eval == 0;

@@ -281,7 +281,8 @@ def test_state_size_is_the_header_and_the_ring():
 
 
 @pytest.mark.parametrize("n,m,d", [(87, 17, 21020), (96, 30, 18944), (116, 24, 14316), (57, 30, 15132),
-                                   (26, 60, 23560), (60, 30, 26380)])
+                                   (26, 60, 23560), (60, 30, 26380), (117, 30, 20308), (60, 70, 16000),
+                                   (103, 40, 8200), (44, 130, 12400)])
 def test_short_partitions_of_wide_rows_do_not_share_gradient_blocks(n, m, d):
     """A block whose rows lie in two partitions leaves a partial sum for each; with few rows per
     block the sums would be a large part of what a step moves.  The workspace holds the ring, the
