@@ -68,13 +68,16 @@ int64_t noalloc_slots(int64_t m, int32_t n_eval) {
 // the one iteration that a crossing costs beyond equal runs (117 of 30 rows of 20,308: 15
 // iterations for 14, 78 us for 86; 66 of 150 of 1,004: 6 for 5, 19.1 for 23.1; but 86 of
 // 60 of 9,000: 15 for 11, 53.1 for 50.4).  Rows of more than kSharedCuFeatures features
-// then take no more blocks than give the longest run its number of iterations: one row
-// more than an iteration takes as long as two, and further blocks only leave more sums to
-// fold (29 partitions of 128 rows of 1,008 features, 4 to an iteration: 493 blocks 12.8 us
-// a step, 464 12.1; 85 of 4 rows of 30,000, one to an iteration: 255 blocks 36.7, 170
-// 31.8).  Narrower rows, of which three or four blocks share a CU, keep their blocks: a
-// sum is little beside a block's rows, and fewer blocks load the CUs unevenly (24 of 900
-// rows of 260: 768 blocks 13.0 us, 696 14.4; 24 of 800 of 700: 768 18.3, 600 19.0).
+// then take no more blocks than give the longest run its number of iterations, where that
+// makes the runs at most a fifth longer: one row more than an iteration takes as long as
+// two, and further blocks only leave more sums to fold (29 partitions of 128 rows of 1,008
+// features, 4 to an iteration: 493 blocks 12.8 us a step, 464 12.1; 40 of 50 of 5,000: 240
+// blocks 20.7, 200 20.0).  Much longer runs would be faster still (5 of 413 of 1,228: 510
+// blocks 11.9, 260 11.1) but sum more rows in 32 bits before the fold's 64: that error
+// grows by 7 to 15%.  Narrower rows, of which three or four blocks share a CU, keep their
+// blocks: a sum is little beside a block's rows, and fewer blocks load the CUs unevenly
+// (24 of 900 rows of 260: 768 blocks 13.0 us, 696 14.4; 24 of 800 of 700: 768 18.3, 600
+// 19.0).
 LinearGrid make_linear_grid(int64_t m, int32_t n_eval, int64_t d) {
   const pgc::LinearGradShape shape = pgc::linear_grad_shape(static_cast<int>(d));
   LinearGrid g;
@@ -82,25 +85,21 @@ LinearGrid make_linear_grid(int64_t m, int32_t n_eval, int64_t d) {
   int64_t blocks = shape.target_blocks;
   const int64_t step = shape.rows_per_iteration;
   const int64_t iterations = (m + step - 1) / step;
-  // A block's, with equal blocks within each partition.
-  auto iterations_within = [&] {
+  auto within = [&] {   // equal blocks of a partition
     const int64_t most = std::max<int64_t>(1, std::min(blocks / n_eval, iterations));
-    return (iterations + most - 1) / most;
+    const int64_t each = (iterations + most - 1) / most, whole = (iterations + each - 1) / each;
+    return d > kSharedCuFeatures && 5 * most <= 6 * whole ? whole : most;
   };
   bool flat = m * n_eval >= blocks * std::max(kFlatIterations * step, kFlatRows);
   if (flat && m * n_eval < blocks * kLongRows)
-    flat = iterations_within() > (m * n_eval + blocks * step - 1) / (blocks * step) + 1;
+    flat = (iterations + within() - 1) / within() > (m * n_eval + blocks * step - 1) / (blocks * step) + 1;
   // pgc_step_noalloc's array holds the sums of every shape it takes.
   const int64_t fit = PGC_NOALLOC_SCRATCH_BYTES / (sizeof(float) * d);
   if (flat && blocks + n_eval - 1 > fit && noalloc_slots(m, n_eval) <= fit) {
     blocks = std::min(blocks, fit);
     flat = false;
   }
-  if (!flat) {
-    const int64_t each = iterations_within();
-    blocks = n_eval * (d > kSharedCuFeatures ? (iterations + each - 1) / each
-                                             : std::max<int64_t>(1, std::min(blocks / n_eval, iterations)));
-  }
+  if (!flat) blocks = n_eval * within();
   g.blocks = static_cast<int32_t>(blocks);
   g.aligned = blocks % n_eval == 0;
   g.wide = shape.folds_wide && blocks / n_eval <= kWidePartials;

@@ -299,24 +299,26 @@ def test_short_partitions_of_wide_rows_do_not_share_gradient_blocks(n, m, d):
         P.pgc_destroy(ctx)
 
 
-@pytest.mark.parametrize("n,m,d,step", [(29, 128, 1008, 4), (5, 413, 1228, 4), (20, 110, 1500, 4), (3, 700, 2040, 4),
-                                        (85, 4, 30000, 1), (64, 5, 20000, 1), (40, 50, 5000, 4), (60, 64, 900, 4)])
-def test_blocks_of_wide_rows_are_no_more_than_their_iterations_need(n, m, d, step):
-    """A block reads `step` rows at a time, and part of them takes as long as all: with one block
-    less per partition the longest run would take an iteration more."""
+@pytest.mark.parametrize("n,m,d,step,blocks", [
+    (29, 128, 1008, 4, 16), (30, 300, 1008, 4, 15), (40, 50, 5000, 4, 5), (66, 150, 1004, 4, 7), (60, 64, 900, 4, 8),
+    (5, 413, 1228, 4, 102), (85, 4, 30000, 1, 3), (64, 5, 20000, 1, 4), (12, 1600, 700, 8, 64)])
+def test_blocks_of_wide_rows_take_whole_iterations_or_no_longer_runs(n, m, d, step, blocks):
+    """A block reads `step` rows at a time, and part of them takes as long as all: rows of more than
+    896 features take no more blocks than their longest run's iterations need, unless the runs would
+    grow by more than a fifth, and with them the rows summed in 32 bits."""
     handle = P.lib()
     size_of = handle["_ZN3pgc21linear_partials_bytesEPK7pgc_ctx"]   # size_t (const pgc_ctx*)
     size_of.restype, size_of.argtypes = ctypes.c_size_t, [ctypes.c_void_p]
     ctx = P.pgc_init("IS_SGD", n, 1, d)
     try:
         P.pgc_configure(ctx, "lsq", n * m, d)
-        partials = size_of(ctx) // (4 * d)
+        assert size_of(ctx) == 4 * d * n * blocks
     finally:
         P.pgc_destroy(ctx)
-    assert partials % n == 0
-    blocks = partials // n
     iterations = lambda b: -(-(-(-m // b)) // step)
-    assert blocks == 1 or iterations(blocks - 1) > iterations(blocks), blocks
+    most = max(1, min((256 if d > 2560 else 512 if d > 896 else 768) // n, -(-m // step)))
+    whole = next(b for b in range(1, most + 1) if iterations(b) <= iterations(most))
+    assert blocks == (whole if d > 896 and 5 * most <= 6 * whole else most)
 
 
 def test_noalloc_step_rejects_on_the_host_before_any_device_work():
